@@ -299,6 +299,15 @@ static void prof_reduce(lrp_ctx* c) {
   }
 }
 
+// The thin QRs of this context's solves run on the column kernels. In FP64 at rank caps above 32 the
+// index sets reach the rounding floor of W^: Q(I,:) then has singular values down to 1e-12, and the
+// cross approximation multiplies the rounding of Q by their reciprocals. Two QRs that agree to 1e-15
+// gave solutions up to 2e-3 apart there (n = 2^20 - 1, 30 bumps, cap 64, identical sets in every
+// pass; 12 seeds, 4 of them above 1e-9), so these solves keep their QR, and with it their results,
+// bit for bit. Below, and in mixed precision, the two QRs' solutions agree: 4e-15 at most over 75
+// FP64 solves at caps 16 and 32, 4e-10 over 135 mixed ones.
+static int keep_column_qr(const lrp_ctx* c) { return c->precision == LRP_FP64 && c->r_max > 32; }
+
 // Pass k up to the stop decision: the set update from the previous candidates, fibers, the
 // two thin QRs, the core, the factor products, rho and the indicator.
 int enqueue_pass_update(lrp_ctx* c, int k) {
@@ -346,6 +355,7 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
+  io.columns = keep_column_qr(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -466,6 +476,7 @@ int enqueue_guess(lrp_ctx* c) {
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
+  io.columns = keep_column_qr(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -548,6 +559,7 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
+  io.columns = keep_column_qr(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -602,6 +614,7 @@ int enqueue_start_matrix(lrp_ctx* c, int r0, const double* U0, int64_t ldu0, con
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
+  io.columns = keep_column_qr(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;

@@ -81,8 +81,9 @@ struct TsqrLevel {
   int64_t rows;      // rows of this level's input
   int block_rows;    // rows per block (<= kTsqrRows)
   int nblocks;
-  double* V[2];      // Householder vectors, rows x p_max (ld = rows), 1 on the diagonal
-  double* tau[2];    // nblocks x p_max
+  double* V[2];      // Householder vectors, rows x p_max values: column-major (ld = rows) with 1 on the
+                     // diagonal, or by panels with their T factors (tsqr_panel.hip)
+  double* tau[2];    // nblocks x p_max (the column kernels)
   double* Rout[2];   // R factors stacked for the next level: (nblocks p_max) x p_max
   double* Y[2];      // top-down output of this level: rows x p_max (ld = rows)
 };

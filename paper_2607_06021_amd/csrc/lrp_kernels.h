@@ -176,10 +176,14 @@ struct TsqrIO {
   int64_t ldx;
   double* Q[2];        // level-0 apply output (n rows), ld ldq; null -> internal Y
   int64_t ldq;
+  int columns;         // 1: the column kernels of tsqr.hip, else the panel kernels (tsqr_panel.hip)
 };
 
 int tsqr_plan(TsqrPlan* p, int64_t n, int pmax);
 int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s);
+// The panel kernels' factorization of level L's blocks, and their part of Q (tsqr_panel.hip).
+int tsqr_panel_factor(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s);
+int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s);
 // Final R of side `side` (pmax x pmax, ld pmax, upper triangular).
 inline const double* tsqr_R(const TsqrPlan& p, int side) { return p.lev[p.nlevels - 1].Rout[side]; }
 

@@ -8,6 +8,10 @@
 // piece of the parent level's Q.
 //
 // Two sides (e.g. C and R^T) are processed by the same launch (blockIdx.y).
+//
+// Two implementations of a level's block work: by 16-column panels (tsqr_panel.hip), which every
+// caller gets but one, and the column kernels of this file, for the solves of keep_column_qr
+// (api.hip).
 #include <mutex>
 
 #include "lrp_kernels.h"
@@ -850,6 +854,17 @@ int tsqr_plan(TsqrPlan* p, int64_t n, int pmax) {
 }
 
 int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
+  if (!io.columns) {  // the panel kernels
+    for (int L = 0; L < p.nlevels; ++L) {
+      const int rc = tsqr_panel_factor(p, L, io, s);
+      if (rc != LRP_OK) return rc;
+    }
+    for (int L = p.nlevels - 1; L >= 0; --L) {
+      const int rc = tsqr_panel_apply(p, L, io, s);
+      if (rc != LRP_OK) return rc;
+    }
+    return LRP_OK;
+  }
   const int ns = io.nsides;
   // bottom-up factorization
   for (int L = 0; L < p.nlevels; ++L) {
