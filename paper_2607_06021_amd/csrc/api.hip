@@ -299,14 +299,15 @@ static void prof_reduce(lrp_ctx* c) {
   }
 }
 
-// The thin QRs of this context's solves run on the column kernels. In FP64 at rank caps above 32 the
-// index sets reach the rounding floor of W^: Q(I,:) then has singular values down to 1e-12, and the
-// cross approximation multiplies the rounding of Q by their reciprocals. Two QRs that agree to 1e-15
-// gave solutions up to 2e-3 apart there (n = 2^20 - 1, 30 bumps, cap 64, identical sets in every
-// pass; 12 seeds, 4 of them above 1e-9), so these solves keep their QR, and with it their results,
-// bit for bit. Below, and in mixed precision, the two QRs' solutions agree: 4e-15 at most over 75
+// This context's solves keep the rounding of everything up to the core: the column kernels for
+// the thin QRs, full-length FFTs in the transforms to the sine basis at general n. In FP64 at rank
+// caps above 32 the index sets reach the rounding floor of W^: Q(I,:) then has singular values down
+// to 1e-12, and the cross approximation multiplies the rounding of Q by their reciprocals. Two QRs
+// that agree to 1e-15 gave solutions up to 2e-3 apart there (n = 2^20 - 1, 30 bumps, cap 64,
+// identical sets in every pass; 12 seeds, 4 of them above 1e-9), so these solves stay bit for bit
+// what they were. Below, and in mixed precision, the two QRs' solutions agree: 4e-15 at most over 75
 // FP64 solves at caps 16 and 32, 4e-10 over 135 mixed ones.
-static int keep_column_qr(const lrp_ctx* c) { return c->precision == LRP_FP64 && c->r_max > 32; }
+static int keep_rounding(const lrp_ctx* c) { return c->precision == LRP_FP64 && c->r_max > 32; }
 
 // Pass k up to the stop decision: the set update from the previous candidates, fibers, the
 // two thin QRs, the core, the factor products, rho and the indicator.
@@ -355,7 +356,7 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
-  io.columns = keep_column_qr(c);
+  io.columns = keep_rounding(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -458,6 +459,7 @@ int enqueue_guess(lrp_ctx* c) {
   da.ncols_out = r0;
   da.Y = c->Uit[1];
   da.ldy = n;
+  da.full_bluestein = keep_rounding(c);
   da.scale = c->guess_S;
   da.outscale = 1.0;
   TRY(dst_launch(c->dst, da, false, s));
@@ -476,7 +478,7 @@ int enqueue_guess(lrp_ctx* c) {
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
-  io.columns = keep_column_qr(c);
+  io.columns = keep_rounding(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -531,6 +533,7 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   da.ldy = n;
   da.st = c->st;
   da.scale = sigma_F;
+  da.full_bluestein = keep_rounding(c);
   da.outscale = h * h;
   if (mixed)
     da.Yf = c->Uh32;
@@ -559,7 +562,7 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
-  io.columns = keep_column_qr(c);
+  io.columns = keep_rounding(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
@@ -614,7 +617,7 @@ int enqueue_start_matrix(lrp_ctx* c, int r0, const double* U0, int64_t ldu0, con
   io.Q[0] = c->Q[0];
   io.Q[1] = c->Q[1];
   io.ldq = n;
-  io.columns = keep_column_qr(c);
+  io.columns = keep_rounding(c);
   TRY(tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;

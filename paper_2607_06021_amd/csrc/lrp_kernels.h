@@ -142,6 +142,7 @@ struct DstArgs {
   double outscale;      // global factor (the launcher folds in 1/sqrt(2N))
   const DevState* st;   // optional: skip after an error; pick_ret selects source/rank
   int pick_ret;
+  int full_bluestein;   // 1: general n by full-length FFTs instead of the odd half (four-step sizes)
   // filled by the launcher
   int pair0;  // first column pair of this launch (pairs are transformed in batches)
   int logL, logL1, logL2;

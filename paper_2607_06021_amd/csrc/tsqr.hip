@@ -10,7 +10,7 @@
 // Two sides (e.g. C and R^T) are processed by the same launch (blockIdx.y).
 //
 // Two implementations of a level's block work: by 16-column panels (tsqr_panel.hip), which every
-// caller gets but one, and the column kernels of this file, for the solves of keep_column_qr
+// caller gets but one, and the column kernels of this file, for the solves of keep_rounding
 // (api.hip).
 #include <mutex>
 
