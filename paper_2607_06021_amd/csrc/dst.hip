@@ -170,16 +170,22 @@ __device__ __forceinline__ void dft(cx<T> (&v)[R]) {
 }
 
 // LDS index with one padding slot per 16 elements (spreads power-of-two strides over banks)
-__device__ __forceinline__ int pad(int p) { return p + (p >> 4); }
-// LDS elements per sequence of length P; odd, so that equal positions of neighbouring
+__host__ __device__ constexpr int pad(int p) { return p + (p >> 4); }
+// LDS reals per sequence of length P; odd, so that equal positions of neighbouring
 // sequences fall in different banks.
 __host__ __device__ constexpr int seq_len(int P) { return P + P / 16 + 1; }
 
 // One Stockham stage of radix R on a sequence of length P whose preceding stages have
 // combined LS points. On entry x[e] is stage input element tt + TP e; on exit x[e] is the
 // stage output in the same layout (through LDS unless this is the last stage).
+//
+// The exchange goes through LDS one component at a time, so a sequence takes P reals. With the
+// padded offsets as immediates and the passes held to 128 VGPRs, two 512-thread workgroups (16 waves)
+// share a CU where whole complex values and 160 VGPRs left one (8 waves); their memory phases cover
+// each other's barriers. FP64, both passes: 56 -> 43 us at n = 65535, 64 columns (134 MB in four
+// passes over memory); 89 -> 67 at n = 262143, 30 columns; 394 -> 372 at n = 2^20 - 1, 30 columns.
 template <typename T, int E, int P, int R, int LS>
-__device__ __forceinline__ void stage(cx<T> (&x)[E], cx<T>* lds, int tt, const cx<T>* __restrict__ tw) {
+__device__ __forceinline__ void stage(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   constexpr int TP = P / E, NB = E / R;
   constexpr bool kLast = (LS * R == P);
   constexpr int TWS = P / (LS * R);  // W_{LS R}^{s k} = W_P^{s k TWS}
@@ -203,22 +209,36 @@ __device__ __forceinline__ void stage(cx<T> (&x)[E], cx<T>* lds, int tt, const c
 #pragma unroll
     for (int e = 0; e < E; ++e) x[e] = y[e];
   } else {
-    __syncthreads();
+    // Output (i, q) goes to pad((b - k) R + k + q LS), b = tt + TP i, k = b mod LS. LS divides TP and
+    // neither q LS nor, where TP R is a multiple of 16, TP R i carries into the padding of the first
+    // output's index, so the padded offsets add up and all but one are immediates.
+    static_assert(TP % LS == 0, "stage order");
+    constexpr bool kLin = NB == 1 || TP * R % 16 == 0, kLinIn = TP % 16 == 0;
+    const int k = tt & (LS - 1);
+    T* out = lds + pad((tt - k) * R + k);
+    T* in = lds + pad(tt);
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int b = tt + TP * i;
-      const int k = b & (LS - 1);
+    for (int part = 0; part < 2; ++part) {
+      __syncthreads();
 #pragma unroll
-      for (int q = 0; q < R; ++q) lds[pad((b - k) * R + k + q * LS)] = y[i + NB * q];
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const T v = part == 0 ? y[i + NB * q].x : y[i + NB * q].y;
+          if (kLin)
+            out[pad(TP * R * i) + pad(q * LS)] = v;
+          else
+            lds[pad((tt - k + TP * i) * R + k + q * LS)] = v;
+        }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < E; ++e) (part == 0 ? x[e].x : x[e].y) = kLinIn ? in[pad(TP * e)] : lds[pad(tt + TP * e)];
     }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) x[e] = lds[pad(tt + TP * e)];
   }
 }
 
 template <typename T, int E, int P, int LS>
-__device__ __forceinline__ void stages16(cx<T> (&x)[E], cx<T>* lds, int tt, const cx<T>* __restrict__ tw) {
+__device__ __forceinline__ void stages16(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   if constexpr (LS < P) {
     stage<T, E, P, 16, LS>(x, lds, tt, tw);
     stages16<T, E, P, LS * 16>(x, lds, tt, tw);
@@ -228,7 +248,7 @@ __device__ __forceinline__ void stages16(cx<T> (&x)[E], cx<T>* lds, int tt, cons
 // Forward DFT of one sequence of length 2^LOGP held as x[e] = element tt + (P/E) e; tw[j] = W_P^j.
 // Every thread of the block must call it (it contains barriers).
 template <typename T, int LOGP, int E>
-__device__ __forceinline__ void fft_seq(cx<T> (&x)[E], cx<T>* lds, int tt, const cx<T>* __restrict__ tw) {
+__device__ __forceinline__ void fft_seq(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   constexpr int P = 1 << LOGP;
   constexpr int R0 = 1 << (LOGP % 4 == 0 ? 4 : LOGP % 4);
   stage<T, E, P, R0, 1>(x, lds, tt, tw);
@@ -279,6 +299,25 @@ __device__ __forceinline__ cx<T> load_z(const double* __restrict__ xa, const dou
   return {va * sg, vb * sg};
 }
 
+// Elements j = off + step e, e < E, of an odd sequence of length E step (off < step): at(base, lane)
+// gives element base + lane of its first half, read for indices 1 .. len-1 only; FULL: len is half the
+// length, so only elements 0 and E/2 step need the test. base is the same for all threads, which keeps
+// the 16 addresses in scalar registers beside two lane offsets (64-bit addresses per element took 30
+// of the vector registers, and with them the second workgroup of a CU).
+template <typename T, int E, bool FULL, typename F>
+__device__ __forceinline__ void load_odd(cx<T> (&x)[E], int64_t step, unsigned off, int64_t len, F at) {
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool neg = e >= E / 2;
+    const int64_t base = step * (neg ? E - 1 - e : e);
+    const unsigned lane = neg ? (unsigned)step - off : off;
+    const bool ok = FULL ? (e == 0 ? off > 0 : e != E / 2 || off > 0) : base + lane >= 1 && base + lane < len;
+    cx<T> v{T(0), T(0)};
+    if (ok) v = at(base, lane);
+    x[e] = neg ? cneg(v) : v;
+  }
+}
+
 // Output k (1..M-1) of the pair: column a gets -Im Z sa, column b gets Re Z sb (0 beyond ncols).
 template <typename T>
 __device__ __forceinline__ void put_pair(const DstArgs& a, int ca, int cb, int ncols, int64_t k, cx<T> Z,
@@ -297,13 +336,15 @@ __device__ __forceinline__ void put_pair(const DstArgs& a, int ca, int cb, int n
 __host__ __device__ constexpr int single_seqs(int logL) {
   return (1 << logL) / 16 >= 64 ? 1 : 64 / ((1 << logL) >= 16 ? (1 << logL) / 16 : 1);
 }
+// LDS index of staged output entry i (row-major rows of the tile's columns): one padding slot per 32
+// entries spreads the column-wise writes over the banks.
+__host__ __device__ constexpr int opad(int i) { return i + (i >> 5); }
 // Largest power-of-two tile (columns per workgroup) with at most `cap` columns, at most 512
-// threads (16 elements each) and at most lds_max bytes of LDS: the whole 160 KB of a CU for the
-// wide tiles (longer row pieces), half of it for the narrow ones (two workgroups per CU).
-constexpr int kLdsWide = 160 * 1024, kLdsNarrow = 80 * 1024;
+// threads (16 elements each) and at most lds_max bytes of LDS (two workgroups per CU).
+constexpr int kLdsTile = 80 * 1024;
 __host__ __device__ constexpr int lds_pass1(int log2, int tj, int esz) { return tj * seq_len(1 << log2) * esz; }
 __host__ __device__ constexpr int lds_pass2(int log1, int tk, int esz) {
-  return (tk * seq_len(1 << log1) > (1 << log1) * (tk + 1) ? tk * seq_len(1 << log1) : (1 << log1) * (tk + 1)) * esz;
+  return (tk * seq_len(1 << log1) > opad(tk << log1) ? tk * seq_len(1 << log1) : opad(tk << log1)) * esz;
 }
 __host__ __device__ constexpr int tile1_for(int log2, int esz, int cap, int lds_max) {
   int t = cap;
@@ -321,11 +362,11 @@ __host__ __device__ constexpr int tile2_for(int log1, int esz, int cap, int lds_
 constexpr int kNarrow1 = 8, kNarrow2 = 4;
 template <typename T, int CAP = 0>
 __host__ __device__ constexpr int tile1_of(int log2) {
-  return tile1_for(log2, (int)sizeof(cx<T>), CAP ? CAP : 32, CAP ? kLdsNarrow : kLdsWide);
+  return tile1_for(log2, (int)sizeof(T), CAP ? CAP : 32, kLdsTile);
 }
 template <typename T, int CAP = 0>
 __host__ __device__ constexpr int tile2_of(int log1) {
-  return tile2_for(log1, (int)sizeof(cx<T>), CAP ? CAP : 16, CAP ? kLdsNarrow : kLdsWide);
+  return tile2_for(log1, (int)sizeof(T), CAP ? CAP : 16, kLdsTile);
 }
 
 // ---------------------------------------------------------------- L <= 4096: one pass
@@ -333,7 +374,7 @@ template <typename T, int LOGL>
 __global__ __launch_bounds__(512) void k_dst_single(DstArgs a) {
   constexpr int L = 1 << LOGL, E = L < 16 ? L : 16, TP = L / E;
   constexpr int SEQS = single_seqs(LOGL), SEQ = seq_len(L);
-  __shared__ cx<T> lds[SEQS * SEQ];
+  __shared__ T lds[SEQS * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
@@ -370,10 +411,10 @@ __device__ __forceinline__ int xcd_order(int b, int nb) {
 // Block: TJ columns j1 (lane-fastest, so global reads and writes are coalesced) x L2/16 threads;
 // TJ = 16 (FP64) or 32 (FP32) columns, so each row of the input is read in 128- or 256-byte pieces.
 template <typename T, int LOG2, int CAP = 0>
-__global__ __launch_bounds__(512) void k_dst_pass1(DstArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_pass1(DstArgs a) {
   constexpr int L2 = 1 << LOG2, E = 16, TP = L2 / E;
   constexpr int TJ = tile1_of<T, CAP>(LOG2), SEQ = seq_len(L2);
-  __shared__ cx<T> lds[TJ * SEQ];
+  __shared__ T lds[TJ * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
@@ -391,23 +432,56 @@ __global__ __launch_bounds__(512) void k_dst_pass1(DstArgs a) {
   const int64_t M = (int64_t)L1 * L2 / 2;
   const int j1 = tile * TJ + cl;
   const bool valid = j1 <= L1 / 2;
-  const double* xa = valid ? X + (int64_t)ca * a.ldx : nullptr;
-  const double* xb = valid && cb < ncols ? X + (int64_t)cb * a.ldx : nullptr;
+  const double* xa = X + (int64_t)ca * a.ldx - 1;
+  const double* xb = cb < ncols ? X + (int64_t)cb * a.ldx - 1 : nullptr;
   cx<T> x[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) x[e] = load_z<T>(xa, xb, M, j1 + (int64_t)L1 * (tt + TP * e));
+  load_odd<T, E, true>(x, (int64_t)L1 * TP, min(j1, L1 / 2) + L1 * tt, M, [&](int64_t base, unsigned lane) {
+    return cx<T>{(T)(xa + base)[lane], xb ? (T)(xb + base)[lane] : T(0)};
+  });
   fft_seq<T, LOG2, E>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
   if (!valid) return;
   const cx<T>* thi = reinterpret_cast<const cx<T>*>(a.t1);  // W_L^{L2 h} = W_L1^h
   const cx<T>* tlo = reinterpret_cast<const cx<T>*>(a.tl);  // W_L^b, b < L2
   cx<T>* S = reinterpret_cast<cx<T>*>(a.work) + (int64_t)pair * L2 * a.s1;
+  int j = j1, t = tt;
+  asm volatile("" : "+v"(j), "+v"(t));  // the twiddle indices are formed here, not before the transform
+  const unsigned at = (unsigned)t * (unsigned)a.s1 + j;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int k2 = tt + TP * e;
-    const bool hi = k2 > L2 / 2;
-    const int64_t m = (int64_t)j1 * (hi ? L2 - k2 : k2);  // <= L/4
+    const int k2 = t + TP * e;
+    if (e % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+    const bool hi = e > E / 2 || (e == E / 2 && t > 0);  // k2 > L2 / 2
+    const int m = j * (hi ? L2 - k2 : k2);  // <= L/4
     const cx<T> w = cmul(thi[m >> LOG2], tlo[m & (L2 - 1)]);
-    S[(int64_t)k2 * a.s1 + j1] = hi ? cneg(cmulc(x[e], w)) : cmul(x[e], w);
+    (S + (int64_t)(TP * e) * a.s1)[at] = hi ? cneg(cmulc(x[e], w)) : cmul(x[e], w);
+  }
+}
+
+// The tile's FFT outputs x[e] (row k1 = tt + TP e of column kl) as the entries that the thread stores:
+// z[i] is entry g = threadIdx.x + NT i of the tile, column g % TK of staged row g / TK.
+// MIRROR: rows k1 >= L1/2 are staged negated and reversed, row L1/2 + m from k1 = L1 - 1 - m.
+// NT is a multiple of the padding's 32, so the padded offsets of e and of i are immediates.
+template <typename T, int L1, int TK, bool MIRROR>
+__device__ __forceinline__ void stage_out(const cx<T> (&x)[16], T* lds, int tt, int kl, cx<T> (&z)[16]) {
+  constexpr int TP = L1 / 16, NT = TK * TP;
+  static_assert(NT % 32 == 0, "padding");
+  T* up = lds + opad(tt * TK + kl);
+  T* down = lds + opad((L1 / 2 + TP - 1 - tt) * TK + kl);
+  T* mine = lds + opad(threadIdx.x);
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const T v = part == 0 ? x[e].x : x[e].y;
+      if (MIRROR && e >= 8)
+        down[opad(NT * (15 - e))] = -v;
+      else
+        up[opad(NT * e)] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) (part == 0 ? z[i].x : z[i].y) = mine[opad(NT * i)];
   }
 }
 
@@ -415,12 +489,11 @@ __global__ __launch_bounds__(512) void k_dst_pass1(DstArgs a) {
 // Block: TK columns k2 (k2 = 0..L2/2) x L1/16 threads (lane-fastest along the sequence, so rows
 // of the intermediate are read contiguously); outputs are staged in LDS and written TK at a time.
 template <typename T, int LOG1, int CAP = 0>
-__global__ __launch_bounds__(512) void k_dst_pass2(DstArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_pass2(DstArgs a) {
   constexpr int L1 = 1 << LOG1, E = 16, TP = L1 / E;
   constexpr int TK = tile2_of<T, CAP>(LOG1), SEQ = seq_len(L1);
-  constexpr int OST = TK + 1;  // staging row stride
-  constexpr int NLDS = TK * SEQ > L1 * OST ? TK * SEQ : L1 * OST;
-  __shared__ cx<T> lds[NLDS];
+  constexpr int NLDS = lds_pass2(LOG1, TK, 1);
+  __shared__ T lds[NLDS];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
@@ -439,8 +512,10 @@ __global__ __launch_bounds__(512) void k_dst_pass2(DstArgs a) {
   col_scales(a, ca, cb, ncols, sa, sb);
   // staged entry g: kl = g % TK, row = g / TK; rows < L1/2 hold Z[k2 + L2 row] of column
   // k2 = k0 + kl, rows L1/2 + m hold Z[(L2 - k2) + L2 m] (already negated).
-  auto write_out = [&](bool zero) {
-    for (int g = threadIdx.x; g < L1 * TK; g += nthreads) {
+  auto write_out = [&](const cx<T>(&z)[16]) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int g = threadIdx.x + nthreads * i;
       const int kl = g % TK, row = g / TK;
       const int k2 = k0 + kl;
       int64_t k;
@@ -452,12 +527,14 @@ __global__ __launch_bounds__(512) void k_dst_pass2(DstArgs a) {
         if (k2 == 0 || k2 >= L2 / 2) continue;
         k = (L2 - k2) + (int64_t)L2 * (row - L1 / 2);
       }
-      const cx<T> Z = zero ? cx<T>{T(0), T(0)} : lds[row * OST + kl];
-      put_pair<T>(a, ca, cb, ncols, k, Z, sa, sb);
+      put_pair<T>(a, ca, cb, ncols, k, z[i], sa, sb);
     }
   };
+  cx<T> z[16];
   if (ca >= ncols) {  // both columns zero
-    write_out(true);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = {T(0), T(0)};
+    write_out(z);
     return;
   }
   const int tt = threadIdx.x % TP, kl = threadIdx.x / TP;
@@ -486,17 +563,8 @@ __global__ __launch_bounds__(512) void k_dst_pass2(DstArgs a) {
     x[e] = v;
   }
   fft_seq<T, LOG1, E>(x, lds + kl * SEQ, tt, t1);
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k1 = tt + TP * e;
-    if (k1 < L1 / 2)
-      lds[k1 * OST + kl] = x[e];
-    else
-      lds[(L1 / 2 + (L1 - 1 - k1)) * OST + kl] = cneg(x[e]);
-  }
-  __syncthreads();
-  write_out(false);
+  stage_out<T, L1, TK, true>(x, lds, tt, kl, z);
+  write_out(z);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -548,7 +616,7 @@ template <typename T, int LOGM>
 __global__ __launch_bounds__(512) void k_dst_bs_single(BsArgs a) {
   constexpr int M = 1 << LOGM, E = 16, TP = M / E;
   constexpr int SEQS = single_seqs(LOGM), SEQ = seq_len(M);
-  __shared__ cx<T> lds[SEQS * SEQ];
+  __shared__ T lds[SEQS * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a.d, X, ncols)) return;
@@ -584,10 +652,10 @@ __global__ __launch_bounds__(512) void k_dst_bs_single(BsArgs a) {
 // j2, the twiddle W_M^{j1 k2}, the intermediate S[k2][j1]. FROM_X: the input is a = z c from the
 // columns; otherwise the buffer B.
 template <typename T, int LOG2, bool FROM_X>
-__global__ __launch_bounds__(512) void k_dst_bs_pass1(BsArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_bs_pass1(BsArgs a) {
   constexpr int M2 = 1 << LOG2, E = 16, TP = M2 / E;
   constexpr int TJ = tile1_of<T>(LOG2), SEQ = seq_len(M2);
-  __shared__ cx<T> lds[TJ * SEQ];
+  __shared__ T lds[TJ * SEQ];
   const double* X = nullptr;
   int ncols = 0;
   if (!a.plain && !dst_resolve(a.d, X, ncols)) return;
@@ -628,12 +696,11 @@ __global__ __launch_bounds__(512) void k_dst_bs_pass1(BsArgs a) {
 // S); outputs staged in LDS so that each row k1 goes out as TK consecutive k2. TO_DST: the DST
 // outputs; otherwise conj(X_k bhat_k) into B (plain: X_k itself).
 template <typename T, int LOG1, bool TO_DST>
-__global__ __launch_bounds__(512) void k_dst_bs_pass2(BsArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_bs_pass2(BsArgs a) {
   constexpr int M1 = 1 << LOG1, E = 16, TP = M1 / E;
   constexpr int TK = tile2_of<T>(LOG1), SEQ = seq_len(M1);
-  constexpr int OST = TK + 1;
-  constexpr int NLDS = TK * SEQ > M1 * OST ? TK * SEQ : M1 * OST;
-  __shared__ cx<T> lds[NLDS];
+  constexpr int NLDS = lds_pass2(LOG1, TK, 1);
+  __shared__ T lds[NLDS];
   const double* X = nullptr;
   int ncols = 0;
   if (!a.plain && !dst_resolve(a.d, X, ncols)) return;
@@ -649,37 +716,32 @@ __global__ __launch_bounds__(512) void k_dst_bs_pass2(BsArgs a) {
   const bool zero = !a.plain && ca >= ncols;
   if (!TO_DST && zero) return;
   const int tt = threadIdx.x % TP, kl = threadIdx.x / TP;
+  cx<T> z[16];
   if (!zero) {
     const cx<T>* S = reinterpret_cast<const cx<T>*>(a.S) + (int64_t)(pair - a.pair0) * M2 * a.s1;
     cx<T> x[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) x[e] = S[(int64_t)(k0 + kl) * a.s1 + tt + TP * e];
     fft_seq<T, LOG1, E>(x, lds + kl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t1));
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) lds[(tt + TP * e) * OST + kl] = x[e];  // row k1, column k2 - k0
-    __syncthreads();
+    stage_out<T, M1, TK, false>(x, lds, tt, kl, z);
   }
-  if (TO_DST) {
-    double sa, sb;
-    col_scales(a.d, ca, cb, ncols, sa, sb);
-    const T invM = T(1.0 / (double)M);
-    for (int g = threadIdx.x; g < M1 * TK; g += nthreads) {
-      const int c = g % TK, k1 = g / TK;
-      const int64_t k = k0 + c + M2 * k1;
+  double sa = 1.0, sb = 1.0;
+  if (TO_DST) col_scales(a.d, ca, cb, ncols, sa, sb);
+  const T invM = T(1.0 / (double)M);
+  const cx<T>* bhat = reinterpret_cast<const cx<T>*>(a.bhat);
+  cx<T>* Bp = reinterpret_cast<cx<T>*>(a.B) + (int64_t)(pair - a.pair0) * M;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int g = threadIdx.x + nthreads * i;
+    const int64_t k = k0 + g % TK + M2 * (g / TK);
+    if (TO_DST) {
       if (k < 1 || k >= a.N) continue;
       if (zero)
         put_pair<T>(a.d, ca, cb, ncols, k, cx<T>{T(0), T(0)}, sa, sb);
       else
-        bs_output<T>(a, ca, cb, ncols, k, lds[k1 * OST + c], invM, sa, sb);
-    }
-  } else {
-    const cx<T>* bhat = reinterpret_cast<const cx<T>*>(a.bhat);
-    cx<T>* Bp = reinterpret_cast<cx<T>*>(a.B) + (int64_t)(pair - a.pair0) * M;
-    for (int g = threadIdx.x; g < M1 * TK; g += nthreads) {
-      const int c = g % TK, k1 = g / TK;
-      const int64_t k = k0 + c + M2 * k1;
-      cx<T> v = lds[k1 * OST + c];
+        bs_output<T>(a, ca, cb, ncols, k, z[i], invM, sa, sb);
+    } else {
+      cx<T> v = z[i];
       if (!a.plain) {
         v = cmul(v, bhat[k]);
         v.y = -v.y;
@@ -711,10 +773,10 @@ __device__ __forceinline__ cx<T> odd_element(int64_t M, int64_t len, int64_t j, 
 // Pass 1 over the columns j1 = 0 .. M1/2 as in k_dst_pass1 (block order, twiddles, intermediate).
 // FROM_X: the input is a = z c from the columns; otherwise the buffer B.
 template <typename T, int LOG2, bool FROM_X, int CAP = 0>
-__global__ __launch_bounds__(512) void k_dst_bs_odd1(BsArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_bs_odd1(BsArgs a) {
   constexpr int M2 = 1 << LOG2, E = 16, TP = M2 / E;
   constexpr int TJ = tile1_of<T, CAP>(LOG2), SEQ = seq_len(M2);
-  __shared__ cx<T> lds[TJ * SEQ];
+  __shared__ T lds[TJ * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a.d, X, ncols)) return;
@@ -729,46 +791,48 @@ __global__ __launch_bounds__(512) void k_dst_bs_odd1(BsArgs a) {
   const int cl = threadIdx.x % TJ, tt = threadIdx.x / TJ;
   const int j1 = tile * TJ + cl;
   const bool valid = j1 <= M1 / 2;
+  const unsigned off = min(j1, M1 / 2) + M1 * tt;
   cx<T> x[E];
   if (FROM_X) {
     const double* xa = X + (int64_t)ca * a.d.ldx;
     const double* xb = cb < ncols ? X + (int64_t)cb * a.d.ldx : nullptr;
     const cx<T>* chirp = reinterpret_cast<const cx<T>*>(a.chirp);
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      x[e] = odd_element<T>(M, valid ? a.N : 0, j1 + (int64_t)M1 * (tt + TP * e), [&](int64_t i) {
-        return cmul(cx<T>{(T)xa[i - 1], xb ? (T)xb[i - 1] : T(0)}, chirp[i]);
-      });
+    load_odd<T, E, false>(x, (int64_t)M1 * TP, off, valid ? a.N : 0, [&](int64_t base, unsigned lane) {
+      const double va = (xa + base - 1)[lane], vb = xb ? (xb + base - 1)[lane] : 0.0;
+      return cmul(cx<T>{(T)va, (T)vb}, (chirp + base)[lane]);
+    });
   } else {
     const cx<T>* Bp = reinterpret_cast<const cx<T>*>(a.B) + (int64_t)lp * (M / 2);
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      x[e] = odd_element<T>(M, valid ? M / 2 : 0, j1 + (int64_t)M1 * (tt + TP * e), [&](int64_t i) { return Bp[i]; });
+    load_odd<T, E, false>(x, (int64_t)M1 * TP, off, valid ? M / 2 : 0,
+                          [&](int64_t base, unsigned lane) { return (Bp + base)[lane]; });
   }
   fft_seq<T, LOG2, E>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
   if (!valid) return;
   const cx<T>* thi = reinterpret_cast<const cx<T>*>(a.t1);  // W_M^{M2 h} = W_M1^h
   const cx<T>* tlo = reinterpret_cast<const cx<T>*>(a.tl);  // W_M^b, b < M2
   cx<T>* S = reinterpret_cast<cx<T>*>(a.S) + (int64_t)lp * M2 * a.s1odd;
+  int j = j1, t = tt;
+  asm volatile("" : "+v"(j), "+v"(t));  // the twiddle indices are formed here, not before the transform
+  const unsigned at = (unsigned)t * (unsigned)a.s1odd + j;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int k2 = tt + TP * e;
-    const bool hi = k2 > M2 / 2;
-    const int64_t m = (int64_t)j1 * (hi ? M2 - k2 : k2);
+    const int k2 = t + TP * e;
+    if (e % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+    const bool hi = e > E / 2 || (e == E / 2 && t > 0);  // k2 > M2 / 2
+    const int m = j * (hi ? M2 - k2 : k2);
     const cx<T> w = cmul(thi[m >> LOG2], tlo[m & (M2 - 1)]);
-    S[(int64_t)k2 * a.s1odd + j1] = hi ? cneg(cmulc(x[e], w)) : cmul(x[e], w);
+    (S + (int64_t)(TP * e) * a.s1odd)[at] = hi ? cneg(cmulc(x[e], w)) : cmul(x[e], w);
   }
 }
 
 // Pass 2 over the columns k2 = 0 .. M2/2 as in k_dst_pass2. TO_DST: the DST outputs c_k v_k with v =
 // -DFT/M; otherwise A_k bhat_k into B, k = 1 .. M/2 - 1.
 template <typename T, int LOG1, bool TO_DST, int CAP = 0>
-__global__ __launch_bounds__(512) void k_dst_bs_odd2(BsArgs a) {
+__global__ __launch_bounds__(512, 4) void k_dst_bs_odd2(BsArgs a) {
   constexpr int M1 = 1 << LOG1, E = 16, TP = M1 / E;
   constexpr int TK = tile2_of<T, CAP>(LOG1), SEQ = seq_len(M1);
-  constexpr int OST = TK + 1;
-  constexpr int NLDS = TK * SEQ > M1 * OST ? TK * SEQ : M1 * OST;
-  __shared__ cx<T> lds[NLDS];
+  constexpr int NLDS = lds_pass2(LOG1, TK, 1);
+  __shared__ T lds[NLDS];
   const double* X;
   int ncols;
   if (!dst_resolve(a.d, X, ncols)) return;
@@ -783,6 +847,7 @@ __global__ __launch_bounds__(512) void k_dst_bs_odd2(BsArgs a) {
   if (TO_DST ? ca >= a.d.ncols_out : zero) return;
   const int k0 = tile * TK;
   const int nthreads = TK * TP;
+  cx<T> z[16];
   if (!zero) {
     const int tt = threadIdx.x % TP, kl = threadIdx.x / TP;
     const int k2 = k0 + kl;
@@ -810,47 +875,34 @@ __global__ __launch_bounds__(512) void k_dst_bs_odd2(BsArgs a) {
       x[e] = v;
     }
     fft_seq<T, LOG1, E>(x, lds + kl * SEQ, tt, t1);
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int k1 = tt + TP * e;
-      if (k1 < M1 / 2)
-        lds[k1 * OST + kl] = x[e];
-      else
-        lds[(M1 / 2 + (M1 - 1 - k1)) * OST + kl] = cneg(x[e]);
-    }
-    __syncthreads();
+    stage_out<T, M1, TK, true>(x, lds, tt, kl, z);
   }
-  // staged rows < M1/2: k = k2 + M2 row; rows M1/2 + m: k = (M2 - k2) + M2 m. The DST's outputs are
-  // k < N < M/4 only: rows m <= N / M2.
+  // staged rows < M1/2: k = k2 + M2 row; rows M1/2 + m: k = (M2 - k2) + M2 m
   double sa = 1.0, sb = 1.0;
   if (TO_DST) col_scales(a.d, ca, cb, ncols, sa, sb);
   const cx<T>* chirp = reinterpret_cast<const cx<T>*>(a.chirp);
   const cx<T>* bhat = reinterpret_cast<const cx<T>*>(a.bhat);
   cx<T>* Bp = reinterpret_cast<cx<T>*>(a.B) + (int64_t)lp * (M / 2);
   const T minvM = T(-1.0 / (double)M);
-  const int rows = TO_DST ? min(M1 / 2, (int)(a.N >> a.d.logL2) + 1) : M1 / 2;  // per half
-  for (int g = threadIdx.x; g < 2 * rows * TK; g += nthreads) {
-    const int kl = g % TK, r = g / TK, row = r < rows ? r : r - rows;
-    const int k2 = k0 + kl;
-    int64_t k;
-    int at;
-    if (r < rows) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int g = threadIdx.x + nthreads * i;
+    const int k2 = k0 + g % TK, row = g / TK;
+    int k;
+    if (row < M1 / 2) {
       if (k2 > M2 / 2) continue;
-      k = k2 + (int64_t)M2 * row;
-      at = row;
+      k = k2 + M2 * row;
     } else {
       if (k2 == 0 || k2 >= M2 / 2) continue;
-      k = (M2 - k2) + (int64_t)M2 * row;
-      at = M1 / 2 + row;
+      k = (M2 - k2) + M2 * (row - M1 / 2);
     }
     if (k == 0) continue;
     if (TO_DST) {
       if (k >= a.N) continue;
-      const cx<T> Z = zero ? cx<T>{T(0), T(0)} : lds[at * OST + kl];
+      const cx<T> Z = zero ? cx<T>{T(0), T(0)} : z[i];
       put_pair<T>(a.d, ca, cb, ncols, k, cmul(chirp[k], cx<T>{Z.x * minvM, Z.y * minvM}), sa, sb);
     } else {
-      Bp[k] = cmul(lds[at * OST + kl], bhat[k]);
+      Bp[k] = cmul(z[i], bhat[k]);
     }
   }
 }
@@ -859,7 +911,7 @@ __global__ __launch_bounds__(512) void k_dst_bs_odd2(BsArgs a) {
 template <int LOGM>
 __global__ __launch_bounds__(256) void k_fft_plain_single(double2* B, const double2* tw) {
   constexpr int M = 1 << LOGM, E = 16, TP = M / E;
-  __shared__ cx<double> lds[seq_len(M)];
+  __shared__ double lds[seq_len(M)];
   const int tt = threadIdx.x;
   cx<double>* Bc = reinterpret_cast<cx<double>*>(B);
   cx<double> x[E];
