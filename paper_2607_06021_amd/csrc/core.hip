@@ -34,45 +34,18 @@ constexpr int kCoreThreads = 512;
 constexpr int kEtaThreads = 512;  // one Jacobi problem of up to 8 waves per workgroup
 constexpr int kBuf = kPMax * LDP;
 
-// ---------------------------------------------------------------- lane-group sums (DPP)
-__device__ inline double dpp_d(double x, int ctrl) {
-  int lo = __double2loint(x), hi = __double2hiint(x);
-  switch (ctrl) {  // the control word must be a compile-time constant
-    case 0xB1:
-      lo = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, false);
-      hi = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, false);
-      break;
-    case 0x4E:
-      lo = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xF, 0xF, false);
-      hi = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xF, 0xF, false);
-      break;
-    case 0x141:
-      lo = __builtin_amdgcn_mov_dpp(lo, 0x141, 0xF, 0xF, false);
-      hi = __builtin_amdgcn_mov_dpp(hi, 0x141, 0xF, 0xF, false);
-      break;
-    default:
-      lo = __builtin_amdgcn_mov_dpp(lo, 0x140, 0xF, 0xF, false);
-      hi = __builtin_amdgcn_mov_dpp(hi, 0x140, 0xF, 0xF, false);
-      break;
-  }
-  return __hiloint2double(hi, lo);
-}
-
-// Sum over aligned groups of G lanes (G = 4, 8 or 16); every lane gets its group's total.
-template <int G>
-__device__ inline double group_sum(double x) {
-  x += dpp_d(x, 0xB1);    // quad_perm [1,0,3,2]
-  x += dpp_d(x, 0x4E);    // quad_perm [2,3,0,1]
-  if (G >= 8) x += dpp_d(x, 0x141);   // row_half_mirror: the other quad of the octet
-  if (G >= 16) x += dpp_d(x, 0x140);  // row_mirror: the other octet of the row
-  return x;
+// ---------------------------------------------------------------- lane moves and sums (DPP)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, false));
 }
 
 // ---------------------------------------------------------------- one-sided Jacobi
 struct JacProb {
-  double* A;  // m x k, column-major, ld LDP (LDS)
+  double* A;  // m x k, m >= k, column-major, ld LDP (LDS), zero elsewhere in 64 x 64
   int m, k;
-  double* V;  // k x k accumulated rotations (holding the identity on entry), or null
+  double* V;  // k x k accumulated rotations (the identity on entry, zero elsewhere in 64 x 64), or null
 };
 
 // Rotation (c, s) that makes columns p, q orthogonal: with al = |a_p|^2, be = |a_q|^2,
@@ -132,228 +105,268 @@ __device__ inline int jac_groups(int k) {
   return g < 2 ? 2 : g;
 }
 
-// One Jacobi pair step on the 16 lanes of a pair slot: lane li holds rows li + 16u (u < 4)
-// of the two columns (a, b) and of their V columns; rows past m (or k for V) are zero, and so is
-// an empty column, which is never rotated (its dot products vanish).
+// A pair slot is a column of lane quads: lanes 16 g + 4 slot + j, g, j < 4, and lane (g, j) holds rows
+// 4 g + j + 16 u, u < U, of the slot's two columns (a, b) and of their V columns; the odd slots run
+// their quads backwards (j = 3 - lane % 4). Rows past m (or k for V) are zero, and so is an empty
+// column, which is never rotated (its dot products vanish). In this layout
+//   * a dot product sums a quad by two DPP steps and the four lane rows by one MFMA (4 x 4 x 4, a
+//     row of ones: 29 cycles, where two more DPP or swap steps take 67);
+//   * the second columns change slots by one DPP move per 32 bits: slot ^ 1 is the mirror of each
+//     octet (the backward quads make its lanes meet their own rows), slot ^ 2 the lane row turned
+//     by 8. The cross-lane permutes through LDS that they replace waited 60 cycles each.
+// U = ceil(m / 16): a lone wave is bound by its instruction count here (a 16-row problem on 64-row
+// code took as long per step as a 64-row one, 1100 cycles).
 constexpr double kJacQuiet2 = 1e-16;  // (1e-8)^2: a rotation below this leaves the next sweep idle
+constexpr int kSlot1 = 0x141;         // row_half_mirror: the lane of slot ^ 1
+constexpr int kSlot2 = 0x128;         // row_ror:8: the lane of slot ^ 2
 
-template <bool WV>
-__device__ inline bool jac_pair(double (&a)[4], double (&b)[4], double (&va)[4], double (&vb)[4], double tol2,
-                                bool& loud) {
+// Sum over a slot's lanes. EXACT: the lane rows are added pairwise, (0 + 1) + (2 + 3), with the
+// rounding that the pseudo-inverse's callers rely on; otherwise in the matrix core's order.
+template <bool EXACT>
+__device__ __forceinline__ double slot_sum(double x) {
+  x += dpp_move<0xB1>(x);  // quad_perm [1,0,3,2]
+  x += dpp_move<0x4E>(x);  // quad_perm [2,3,0,1]
+  if (!EXACT) return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, x, 0.0, 0, 0, 0);
+  const int lane = threadIdx.x & 63;
+  x += lane_fetch(x, lane ^ 16);
+  return x + lane_fetch(x, lane ^ 32);
+}
+
+template <bool WV, int U, bool EXACT>
+__device__ __forceinline__ void jac_pair(double (&a)[U], double (&b)[U], double (&va)[U], double (&vb)[U],
+                                         double tol2, bool& loud) {
   double al = 0.0, be = 0.0, ga = 0.0;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < U; ++u) {
     al = fma(a[u], a[u], al);
     be = fma(b[u], b[u], be);
     ga = fma(a[u], b[u], ga);
   }
-  al = group_sum<16>(al);
-  be = group_sum<16>(be);
-  ga = group_sum<16>(ga);
+  al = slot_sum<EXACT>(al);
+  be = slot_sum<EXACT>(be);
+  ga = slot_sum<EXACT>(ga);
   const bool rot = ga != 0.0 && ga * ga > tol2 * al * be;
   loud |= rot && ga * ga > kJacQuiet2 * al * be;
   // Straight-line rotation for every slot (slots that do not rotate take c = 1, s = 0, which
-  // leaves the values of their columns unchanged); the extreme-range formula is a rare branch.
+  // leaves the values of their columns unchanged); the extreme-range formula is out of line.
   const double d = be - al, g2 = 2.0 * ga;
   const double h2 = fma(d, d, g2 * g2);
   const double h = h2 * rsq_nr(h2);
   const double uu = h + fabs(d);
   const double rr = rsq_nr(2.0 * h * uu);
   double c = uu * rr, sn = copysign(1.0, d) * g2 * rr;
-  if (rot && !(h2 > 1e-290 && h2 < 1e290)) jacobi_rotation(al, be, ga, c, sn);
+  const bool rare = rot && !(h2 > 1e-290 && h2 < 1e290);
+  if (__builtin_expect(__ballot(rare) != 0, 0)) {
+    if (rare) jacobi_rotation(al, be, ga, c, sn);
+  }
   c = rot ? c : 1.0;
   sn = rot ? sn : 0.0;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < U; ++u) {
     const double x = a[u], y = b[u];
     a[u] = c * x - sn * y;
     b[u] = sn * x + c * y;
   }
   if (WV) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       const double x = va[u], y = vb[u];
       va[u] = c * x - sn * y;
       vb[u] = sn * x + c * y;
     }
   }
-  return rot;
 }
 
-// The second columns of every slot (and their V columns) move to the slot of lane ^ xmask.
-template <bool WV>
-__device__ inline void jac_move_b(double (&b)[4], double (&vb)[4], int src) {
+// The second columns of every slot (and their V columns) move to slot ^ 1 or slot ^ 2.
+template <bool WV, int U, int CTRL>
+__device__ __forceinline__ void jac_move_b(double (&b)[U], double (&vb)[U]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    b[u] = lane_fetch(b[u], src);
-    if (WV) vb[u] = lane_fetch(vb[u], src);
+  for (int u = 0; u < U; ++u) {
+    b[u] = dpp_move<CTRL>(b[u]);
+    if (WV) vb[u] = dpp_move<CTRL>(vb[u]);
   }
 }
 
-// Column col (into x, vx) from LDS, zero past the problem. Every address lies in the 64 x LDP
-// buffer (col < 64, rows < 64), so all loads are issued unconditionally and the entries outside
-// the problem are replaced afterwards; the empty asm statements keep the selects from being
-// turned back into branches around single loads.
-template <bool WV>
-__device__ inline void jac_load(const JacProb& pr, int col, int li, double (&x)[4], double (&vx)[4]) {
-  const bool ok = col < pr.k;
+// A column (into x, vx) from LDS and back; off: the column's and the lane's offset. Every address
+// lies in the 64 x LDP buffers, whose entries past the problem are zero and stay so.
+template <bool WV, int U>
+__device__ __forceinline__ void jac_load(const JacProb& pr, int off, double (&x)[U], double (&vx)[U]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    x[u] = pr.A[li + 16 * u + col * LDP];
-    if (WV) vx[u] = pr.V[li + 16 * u + col * LDP];
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = li + 16 * u;
-    asm volatile("" : "+v"(x[u]));
-    x[u] = (ok && i < pr.m) ? x[u] : 0.0;
-    if (WV) {
-      asm volatile("" : "+v"(vx[u]));
-      vx[u] = (ok && i < pr.k) ? vx[u] : 0.0;
-    }
+  for (int u = 0; u < U; ++u) {
+    x[u] = pr.A[off + 16 * u];
+    if (WV) vx[u] = pr.V[off + 16 * u];
   }
 }
 
-template <bool WV>
-__device__ inline void jac_store(const JacProb& pr, int col, int li, const double (&x)[4], const double (&vx)[4]) {
-  if (col >= pr.k) return;
+template <bool WV, int U>
+__device__ __forceinline__ void jac_store(const JacProb& pr, int off, const double (&x)[U], const double (&vx)[U]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = li + 16 * u;
-    if (i < pr.m) pr.A[i + col * LDP] = x[u];
-    if (WV && i < pr.k) pr.V[i + col * LDP] = vx[u];
+  for (int u = 0; u < U; ++u) {
+    pr.A[off + 16 * u] = x[u];
+    if (WV) pr.V[off + 16 * u] = vx[u];
   }
 }
 
-// Solve one or two independent Jacobi problems (A: m x k in LDS, m, k <= 64; V: the k x k
-// accumulated rotations, holding the identity on entry, or null for none) with the workgroup:
-// problem q runs on waves 8q .. 8q+7 (blockDim.x >= 512 nprob). flags: 2 ints of LDS.
+// Solve a Jacobi problem (A: m x k in LDS, m, k <= 64; V: the k x k accumulated rotations, holding
+// the identity on entry, or null for none) with the workgroup (at least 8 waves). flags: 2 ints of
+// LDS.
 //
 // The k columns are split into NG groups of 4 (NG even, columns past k empty). A sweep is
 //   * NG - 1 group rounds: the round-robin (circle) schedule over the groups gives wave w the
-//     group pair (g, h); the wave loads the 8 columns into registers -- pair slot i (lanes
-//     16i .. 16i+15) takes columns 4g + i and 4h + i -- and runs 4 rounds pairing 4g + i with
-//     4h + (i ^ s), s = 0, 1, 3, 2, the second columns moving between slots by lane permutes,
-//     then stores them back (one workgroup barrier per group round);
+//     group pair (g, h); the wave loads the 8 columns into registers -- pair slot i takes columns
+//     4g + i and 4h + i -- and runs 4 rounds pairing 4g + i with 4h + (i ^ s), s = 0, 1, 3, 2,
+//     the second columns moving between slots, then stores them back (one workgroup barrier per
+//     group round);
 //   * an intra-group phase: wave w takes groups 2w and 2w+1 and pairs the 4 columns of each in 3
 //     rounds ((0,1)(2,3), (0,2)(1,3), (0,3)(1,2)).
 // Every column pair is visited once per sweep, no two pairs of a round share a column, and no
 // barrier is needed inside a group round.
-template <bool WV>
-__device__ int jacobi_waves(JacProb* P, int nprob, int* flags) {
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int q = (nprob == 2 && wv >= 8) ? 1 : 0;
-  const int lw = wv - 8 * q;
-  const JacProb pr = P[q];
-  const int slot = lane >> 4, li = lane & 15;
-  int ngmax = 0, kmax = 0;
-  for (int x = 0; x < nprob; ++x) {
-    kmax = max(kmax, P[x].k);
-    ngmax = max(ngmax, jac_groups(P[x].k));
-  }
-  if (kmax < 2) {
+//
+// Bound by the instruction issue of one wave per SIMD (two at k > 32: 33 to 40 columns make 5 waves, and
+// two of them share a SIMD). Cycles per pair step with V, before this layout and the row classes, and
+// now: 16 columns 1100 -> 620, 32 columns 1140 -> 790, 37 columns 1500 -> 1260, 64 columns 1690 -> 1640.
+// The whole core step at 16, 32 and 37 columns: 66 -> 44, 139 -> 103 and 230 -> 195 us.
+template <bool WV, int U, bool EXACT>
+__device__ int jacobi_waves(const JacProb& pr, int* flags) {
+  const int t = threadIdx.x, lane = t & 63;
+  const int lw = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int slot = (lane >> 2) & 3;
+  const int li = 4 * (lane >> 4) + ((slot & 1) ? 3 - (lane & 3) : lane & 3);
+  if (pr.k < 2) {
     __syncthreads();
     return 0;
   }
   const int ng = jac_groups(pr.k);
-  const bool mine = pr.k >= 2 && lw < (ng >> 1) && (nprob == 2 || wv < 8);
+  const bool mine = lw < (ng >> 1);
   const double tol = sqrt((double)max(pr.m, 1)) * kEps;
   const double tol2 = tol * tol;
-  double a[4], b[4], va[4], vb[4];
-  bool active = true;  // this problem's last sweep made a rotation above the quiet level
+  double a[U], b[U], va[U], vb[U];
   int sweeps = 0;
+  if (t < 2) flags[t] = 0;
+  __syncthreads();
   for (int sweep = 0; sweep < 60; ++sweep) {
     sweeps = sweep + 1;
-    if (t < 2) flags[t] = 0;
-    __syncthreads();
-    bool loud = false;
-    for (int gr = 0; gr < ngmax - 1; ++gr) {
-      if (active && mine && gr < ng - 1) {
+    bool loud = false;  // a rotation above the quiet level
+    for (int gr = 0; gr < ng - 1; ++gr) {
+      if (mine) {
         int g, h;
         rr_pair(ng, lw, gr, g, h);
-        jac_load<WV>(pr, 4 * g + slot, li, a, va);
-        jac_load<WV>(pr, 4 * h + slot, li, b, vb);
-        jac_pair<WV>(a, b, va, vb, tol2, loud);  // s = 0
-        jac_move_b<WV>(b, vb, lane ^ 16);
-        jac_pair<WV>(a, b, va, vb, tol2, loud);  // s = 1
-        jac_move_b<WV>(b, vb, lane ^ 32);
-        jac_pair<WV>(a, b, va, vb, tol2, loud);  // s = 3
-        jac_move_b<WV>(b, vb, lane ^ 16);
-        jac_pair<WV>(a, b, va, vb, tol2, loud);  // s = 2
-        jac_store<WV>(pr, 4 * g + slot, li, a, va);
-        jac_store<WV>(pr, 4 * h + (slot ^ 2), li, b, vb);
+        const int oa = li + (4 * g + slot) * LDP, ob = li + (4 * h + slot) * LDP;
+        jac_load<WV, U>(pr, oa, a, va);
+        jac_load<WV, U>(pr, ob, b, vb);
+        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 0
+        jac_move_b<WV, U, kSlot1>(b, vb);
+        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 1
+        jac_move_b<WV, U, kSlot2>(b, vb);
+        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 3
+        jac_move_b<WV, U, kSlot1>(b, vb);
+        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 2
+        jac_store<WV, U>(pr, oa, a, va);
+        jac_store<WV, U>(pr, li + (4 * h + (slot ^ 2)) * LDP, b, vb);
       }
       __syncthreads();
     }
-    if (active && mine) {
+    if (mine) {
       const int c0 = 4 * (2 * lw + (slot >> 1));
       const bool odd = slot & 1;
-      jac_load<WV>(pr, c0 + (odd ? 2 : 0), li, a, va);
-      jac_load<WV>(pr, c0 + (odd ? 3 : 1), li, b, vb);
-      jac_pair<WV>(a, b, va, vb, tol2, loud);  // (0,1) (2,3)
+      jac_load<WV, U>(pr, li + (c0 + (odd ? 2 : 0)) * LDP, a, va);
+      jac_load<WV, U>(pr, li + (c0 + (odd ? 3 : 1)) * LDP, b, vb);
+      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,1) (2,3)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {  // even slot: b <- partner's a; odd slot: a <- partner's b
-        const double ta = lane_fetch(a[u], lane ^ 16), tb = lane_fetch(b[u], lane ^ 16);
-        if (odd)
-          a[u] = tb;
-        else
-          b[u] = ta;
+      for (int u = 0; u < U; ++u) {  // even slot: b <- partner's a; odd slot: a <- partner's b
+        const double x = dpp_move<kSlot1>(odd ? a[u] : b[u]);
+        a[u] = odd ? x : a[u];
+        b[u] = odd ? b[u] : x;
         if (WV) {
-          const double tva = lane_fetch(va[u], lane ^ 16), tvb = lane_fetch(vb[u], lane ^ 16);
-          if (odd)
-            va[u] = tvb;
-          else
-            vb[u] = tva;
+          const double s1 = dpp_move<kSlot1>(odd ? va[u] : vb[u]);
+          va[u] = odd ? s1 : va[u];
+          vb[u] = odd ? vb[u] : s1;
         }
       }
-      jac_pair<WV>(a, b, va, vb, tol2, loud);  // (0,2) (1,3)
-      jac_move_b<WV>(b, vb, lane ^ 16);
-      jac_pair<WV>(a, b, va, vb, tol2, loud);  // (0,3) (1,2)
-      jac_store<WV>(pr, c0 + (odd ? 1 : 0), li, a, va);
-      jac_store<WV>(pr, c0 + (odd ? 2 : 3), li, b, vb);
+      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,2) (1,3)
+      jac_move_b<WV, U, kSlot1>(b, vb);
+      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,3) (1,2)
+      jac_store<WV, U>(pr, li + (c0 + (odd ? 1 : 0)) * LDP, a, va);
+      jac_store<WV, U>(pr, li + (c0 + (odd ? 2 : 3)) * LDP, b, vb);
+      if (__ballot(loud) != 0 && lane == 0) flags[sweep & 1] = 1;
     }
-    if (loud) flags[q] = 1;
     __syncthreads();
-    const bool any0 = flags[0] != 0, any1 = flags[1] != 0;
-    active = q == 0 ? any0 : any1;
-    const bool more = any0 || (nprob == 2 && any1);
-    __syncthreads();
+    const bool more = flags[sweep & 1] != 0;
+    if (t == 0) flags[(sweep + 1) & 1] = 0;  // set again only past the next sweep's first barrier
     if (!more) break;
   }
   return sweeps;
 }
 
-// Returns the number of sweeps made (the last one made no rotation above the quiet level).
-__device__ int jacobi(JacProb* P, int nprob, int* flags) {
-  bool wv = false;
-  for (int x = 0; x < nprob; ++x) wv |= P[x].V != nullptr;
-  if (wv) return jacobi_waves<true>(P, nprob, flags);
-  return jacobi_waves<false>(P, nprob, flags);
+// Returns the number of sweeps made (the last one made no rotation above the quiet level). EXACT:
+// see slot_sum.
+template <bool WV>
+__device__ __forceinline__ int jacobi(const JacProb& pr, int* flags) {
+  switch ((pr.m + 15) >> 4) {  // uniform; m >= k
+    case 0:
+    case 1: return jacobi_waves<WV, 1, false>(pr, flags);
+    case 2: return jacobi_waves<WV, 2, false>(pr, flags);
+    case 3: return jacobi_waves<WV, 3, false>(pr, flags);
+    default: return jacobi_waves<WV, 4, false>(pr, flags);
+  }
 }
 
-// sig[c] = ||A(:, c)||, ord[r] = column of rank r (descending, ties to the smaller index).
-__device__ void norms_sorted(const double* A, int m, int k, double* sig, int* ord) {
+// sig[c] = ||A(:, c)||, ord[r] = column of rank r (descending, ties to the smaller index), srt[r] its
+// norm (0 past k). A is zero past its m rows. Sums and searches run 8 at a time, so that their LDS reads
+// are in flight together (one wait each took 100 cycles).
+__device__ void norms_sorted(const double* A, int m, int k, double* sig, int* ord, double* srt) {
   const int t = threadIdx.x;
-  if (t < k) {
+  if (t < kPMax) {
     double s = 0.0;
-    for (int i = 0; i < m; ++i) s = fma(A[i + t * LDP], A[i + t * LDP], s);
-    sig[t] = sqrt(s);
+    if (t < k) {
+      for (int i0 = 0; i0 < m; i0 += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = A[i0 + u + t * LDP];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s = fma(x[u], x[u], s);
+      }
+    }
+    sig[t] = t < k ? sqrt(s) : -1.0;
+    srt[t] = 0.0;
   }
   __syncthreads();
   if (t < k) {
     const double v = sig[t];
     int rk = 0;
-    for (int c = 0; c < k; ++c) rk += (sig[c] > v || (sig[c] == v && c < t)) ? 1 : 0;
+    for (int c0 = 0; c0 < k; c0 += 8) {  // the entries past k, -1, are behind every norm
+#pragma unroll
+      for (int u = 0; u < 8; ++u) rk += (sig[c0 + u] > v || (sig[c0 + u] == v && c0 + u < t)) ? 1 : 0;
+    }
     ord[rk] = t;
+    srt[rk] = v;
   }
   __syncthreads();
 }
 
-__device__ void set_identity(double* V, int k) {
-  for (int e = threadIdx.x; e < k * LDP; e += blockDim.x) {
-    const int i = e % LDP, j = e / LDP;
-    V[e] = (i == j) ? 1.0 : 0.0;
+// sum_{l < r} srt[l]^2 in order.
+__device__ inline double sorted_norm2(const double* srt, int r) {
+  double n2 = 0.0;
+  for (int l0 = 0; l0 < r; l0 += 8) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = l0 + u < r ? srt[l0 + u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) n2 = fma(x[u], x[u], n2);
   }
+  return n2;
+}
+
+// The k x k identity, zero elsewhere in 64 x 64.
+__device__ void set_identity(double* V, int k) {
+  for (int e = threadIdx.x; e < kBuf; e += blockDim.x) {
+    const int i = e % LDP, j = e / LDP;
+    V[e] = (i == j && j < k) ? 1.0 : 0.0;
+  }
+}
+
+__device__ void zero_block(double* S) {
+  for (int e = threadIdx.x; e < kBuf; e += blockDim.x) S[e] = 0.0;
 }
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -363,21 +376,23 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 __device__ inline void pin(double& v) { asm volatile("" : "+v"(v)); }
 
 // C = A B for 64 x 64 matrices in LDS (column-major, ld LDP, zero outside the used m x k and
-// k x n parts) on the FP64 matrix cores (v_mfma_f64_16x16x4: operand A lane l = A(l%16, l/16),
+// k x n parts; inner: a bound on k) on the FP64 matrix cores (v_mfma_f64_16x16x4: operand A lane l = A(l%16, l/16),
 // B lane l = B(l/16, l%16), result item v = C(l/16 + 4v, l%16)): the 16 tiles of 16 x 16 go
 // round the waves of the workgroup. C(i, j), i < m, j < n, is stored at C[i + j LDP], or at
 // C[j + i LDP] when trans. C must not overlap A or B.
-__device__ void lds_gemm(const double* A, const double* B, double* C, int m, int n, bool trans) {
+__device__ void lds_gemm(const double* A, const double* B, double* C, int m, int n, int inner, bool trans) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   for (int q = wave; q < 16; q += nw) {
     const int I = q >> 2, J = q & 3;
     if (16 * I >= m || 16 * J >= n) continue;
     f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < inner; k0 += 16) {
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[16 * I + lr + (4 * ks + lk) * LDP],
-                                                  B[4 * ks + lk + (16 * J + lr) * LDP], acc, 0, 0, 0);
+      for (int ks = 0; ks < 4; ++ks)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[16 * I + lr + (k0 + 4 * ks + lk) * LDP],
+                                                    B[k0 + 4 * ks + lk + (16 * J + lr) * LDP], acc, 0, 0, 0);
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = 16 * I + lk + 4 * v, j = 16 * J + lr;
@@ -430,32 +445,19 @@ __device__ void load_block(const double* F, int64_t ldf, int m, int k, double* S
 // The small dense routines below keep one column per 8 lanes (rows li + 8u, u < 8, in
 // registers; with 512 threads the 64 columns are covered in one pass).
 
-// x[u] for a u that is the same on every active lane (a scalar branch, not a select chain).
-__device__ inline double pick8(const double (&x)[8], int u) {
-  switch (u & 7) {
-    case 0: return x[0];
-    case 1: return x[1];
-    case 2: return x[2];
-    case 3: return x[3];
-    case 4: return x[4];
-    case 5: return x[5];
-    case 6: return x[6];
-    default: return x[7];
-  }
-}
-
 // In place on A (m x k, m >= k, ld LDP): R in the upper triangle, the reflectors' tails below
 // (LAPACK convention: beta = -sign(alpha) ||x||, tau = (beta - alpha)/beta, v = x/(alpha - beta),
 // v_j = 1 implicit), tau[j] in LDS. Column j builds its reflector from its registers (tau =
 // 1 + |alpha|/h and 1/(alpha - beta) = sign(alpha)/(|alpha| + h) with h = ||x||, one rsq and one
 // rcp), publishes it in LDS (vb: 2 x 64 doubles, double-buffered) and after one barrier every
-// trailing column applies it. blockDim.x >= 512.
-__device__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
+// trailing column applies it. blockDim.x >= 512. U = ceil(m / 8), rounded up to even.
+template <int U>
+__device__ void small_qr_rows(double* A, int m, int k, double* tau, double* vb) {
   const int t = threadIdx.x, c = t >> 3, li = t & 7;
   const bool col = c < k;
-  double x[8];
+  double x[U];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
+  for (int u = 0; u < U; ++u) {
     const int i = li + 8 * u;
     x[u] = (col && i < m) ? A[i + c * LDP] : 0.0;
   }
@@ -463,14 +465,14 @@ __device__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
   for (int j = 0; j < k; ++j) {
     double* vj = vb + (j & 1) * kPMax;
     if (c == j) {
-      double y[8], n[4] = {0.0, 0.0, 0.0, 0.0};
+      double y[U], n[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         y[u] = li + 8 * u > j ? x[u] : 0.0;
         n[u & 3] = fma(y[u], y[u], n[u & 3]);
       }
       const double xnorm2 = oct_sum((n[0] + n[1]) + (n[2] + n[3]));
-      const double xj = pick8(x, j >> 3);
+      const double xj = x[j >> 3];  // the same register for every lane
       const int src = ((j & 7) << 3) + (j & 7);  // lane of row j within column j's octet
       const double alpha = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xj), src),
                                             __builtin_amdgcn_readlane(__double2loint(xj), src)) +
@@ -491,7 +493,7 @@ __device__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
         scale = 1.0 / (alpha - beta);
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) vj[li + 8 * u] = y[u] * scale;
+      for (int u = 0; u < U; ++u) vj[li + 8 * u] = y[u] * scale;
       if (li == (j & 7)) vj[j] = 1.0;  // same lane, after its zero: in order
       rdiag = beta;
       vscale = scale;
@@ -499,20 +501,20 @@ __device__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
     }
     __syncthreads();
     if (c > j && col) {
-      double v[8], d[4] = {0.0, 0.0, 0.0, 0.0};
+      double v[U], d[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         v[u] = vj[li + 8 * u];
         d[u & 3] = fma(v[u], x[u], d[u & 3]);
       }
       const double w = oct_sum((d[0] + d[1]) + (d[2] + d[3])) * tau[j];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = fma(-w, v[u], x[u]);
+      for (int u = 0; u < U; ++u) x[u] = fma(-w, v[u], x[u]);
     }
   }
   if (col) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = li + 8 * u;
       if (i < m) A[i + c * LDP] = i < c ? x[u] : (i == c ? rdiag : x[u] * vscale);
     }
@@ -520,39 +522,68 @@ __device__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
   __syncthreads();
 }
 
+__device__ __forceinline__ void small_qr(double* A, int m, int k, double* tau, double* vb) {
+  switch ((m + 15) >> 4) {  // uniform
+    case 0:
+    case 1: return small_qr_rows<2>(A, m, k, tau, vb);
+    case 2: return small_qr_rows<4>(A, m, k, tau, vb);
+    case 3: return small_qr_rows<6>(A, m, k, tau, vb);
+    default: return small_qr_rows<8>(A, m, k, tau, vb);
+  }
+}
+
 // B (m x ncols, ld LDP) <- H_{k-1} .. H_0 B (Q2-full^T B) if transpose, else H_0 .. H_{k-1} B,
 // with V holding the reflectors explicitly (unit diagonal, zeros above and below row m - 1: see
 // explicit_reflectors). Every column runs through the k reflectors on its own lanes.
-__device__ void apply_reflectors(const double* V, const double* tau, int m, int k, double* B, int ncols,
-                                 bool transpose) {
+template <int U>
+__device__ void apply_reflectors_rows(const double* V, const double* tau, int m, int k, double* B, int ncols,
+                                      bool transpose) {
   const int t = threadIdx.x, li = t & 7;
   for (int c = t >> 3; c < ncols; c += blockDim.x >> 3) {
-    double x[8];
+    double x[U], vn[U], tn = 0.0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = li + 8 * u;
       x[u] = i < m ? B[i + c * LDP] : 0.0;
     }
-    for (int s = 0; s < k; ++s) {
+    auto fetch = [&](int s) {  // reflector s of the sequence, one step ahead of its use
       const int j = transpose ? s : k - 1 - s;
-      const double* vj = V + j * LDP + li;
-      double v[8], d[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        v[u] = vj[8 * u];
-        d[u & 3] = fma(v[u], x[u], d[u & 3]);
-      }
-      const double w = oct_sum((d[0] + d[1]) + (d[2] + d[3])) * tau[j];
+      for (int u = 0; u < U; ++u) vn[u] = V[j * LDP + li + 8 * u];
+      tn = tau[j];
+    };
+    if (k > 0) fetch(0);
+#pragma unroll 2
+    for (int s = 0; s < k; ++s) {
+      double v[U], d[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = fma(-w, v[u], x[u]);
+      for (int u = 0; u < U; ++u) v[u] = vn[u];
+      const double tj = tn;
+      fetch(min(s + 1, k - 1));
+#pragma unroll
+      for (int u = 0; u < U; ++u) d[u & 3] = fma(v[u], x[u], d[u & 3]);
+      const double w = oct_sum((d[0] + d[1]) + (d[2] + d[3])) * tj;
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = fma(-w, v[u], x[u]);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = li + 8 * u;
       if (i < m) B[i + c * LDP] = x[u];
     }
   }
   __syncthreads();
+}
+
+__device__ __forceinline__ void apply_reflectors(const double* V, const double* tau, int m, int k, double* B,
+                                                 int ncols, bool transpose) {
+  switch ((m + 15) >> 4) {  // uniform
+    case 0:
+    case 1: return apply_reflectors_rows<2>(V, tau, m, k, B, ncols, transpose);
+    case 2: return apply_reflectors_rows<4>(V, tau, m, k, B, ncols, transpose);
+    case 3: return apply_reflectors_rows<6>(V, tau, m, k, B, ncols, transpose);
+    default: return apply_reflectors_rows<8>(V, tau, m, k, B, ncols, transpose);
+  }
 }
 
 // Overwrites the R part of a small_qr result with the explicit reflectors: 1 on the diagonal,
@@ -590,11 +621,13 @@ __device__ __forceinline__ void tri_inverse(const double* QR, int k, double* Ri,
       for (int w = 0; w < 16; ++w) x[w] = Ri[(r0 + w) + lane * LDP];
 #pragma unroll
       for (int w = 15; w >= 0; --w) {
-        const double z = dinv[r0 + w] * x[w];  // zero past k
-        Ri[(r0 + w) + lane * LDP] = z;
+        x[w] *= dinv[r0 + w];  // zero past k
 #pragma unroll
-        for (int w2 = 0; w2 < w; ++w2) x[w2] = fma(-QR[(r0 + w2) + (r0 + w) * LDP], z, x[w2]);
+        for (int w2 = 0; w2 < w; ++w2) x[w2] = fma(-QR[(r0 + w2) + (r0 + w) * LDP], x[w], x[w2]);
       }
+      // stored only now: a store between the steps would hold back the reads of R behind it
+#pragma unroll
+      for (int w = 0; w < 16; ++w) Ri[(r0 + w) + lane * LDP] = x[w];
     }
     __syncthreads();
     if (b == 0) break;
@@ -654,7 +687,7 @@ __device__ void tri_norms(const double* QR, const double* Ri, int k, double* red
 // sweeps in *sweeps. Mb, Xb, Vq, Cb are distinct 64 x 64 LDS buffers (Mb, Vq are overwritten);
 // tau: kPMax, vbq: 2 kPMax doubles.
 __device__ __forceinline__ int svd_qr(double* Mb, int nJ, int nI, double cut_mult, double* Xb, double* Vq, double* Cb,
-                      double* tau, double* vbq, double* sig, int* ord, int* flags, int* sweeps) {
+                      double* tau, double* vbq, double* sig, int* ord, double* srt, int* flags, int* sweeps) {
   const int t = threadIdx.x;
   const bool tall = nJ >= nI;
   const int m = tall ? nJ : nI, k = tall ? nI : nJ;
@@ -671,20 +704,18 @@ __device__ __forceinline__ int svd_qr(double* Mb, int nJ, int nI, double cut_mul
   }
   __syncthreads();
   JacProb pr{Mb, k, k, Vq};
-  *sweeps = jacobi(&pr, 1, flags);
-  norms_sorted(Mb, k, k, sig, ord);
-  const double smax = k > 0 ? sig[ord[0]] : 0.0;
-  int r = 0;
-  if (smax > 0.0) {
-    const double cut = cut_mult * kEps * smax;
-    for (int c = 0; c < k; ++c) r += sig[ord[c]] > cut ? 1 : 0;
-  }
+  *sweeps = jacobi<true>(pr, flags);
+  norms_sorted(Mb, k, k, sig, ord, srt);
+  const double smax = k > 0 ? srt[0] : 0.0;
+  const double cut = cut_mult * kEps * smax;
+  const int lane = t & 63;  // every wave counts the kept values
+  const int r = smax > 0.0 ? __popcll(__ballot(lane < k && srt[lane] > cut)) : 0;
   explicit_reflectors(Xb, m, k);
   apply_reflectors(Xb, tau, m, k, Vq, k, false);  // Vq <- Q [V; 0]
   for (int e = t; e < r * kPMax; e += blockDim.x) {
     const int i = e % kPMax, rr = e / kPMax;
     const int c = ord[rr];
-    const double inv = 1.0 / sig[c];
+    const double inv = 1.0 / srt[rr];
     const double left = i < m ? Vq[i + c * LDP] : 0.0;
     const double right = i < k ? Mb[i + c * LDP] * inv : 0.0;
     Cb[i + rr * LDP] = tall ? left : right;
@@ -700,7 +731,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   DevState* st = a.st;
   if (st->done) return;
   __shared__ double B0[kBuf], B1[kBuf], B2[kBuf], B3[kBuf];
-  __shared__ double sig[kPMax], tau[kPMax], red[16], nrm2[2], vbq[2 * kPMax], dinv[kPMax];
+  __shared__ double sig[kPMax], srt[kPMax], tau[kPMax], red[16], nrm2[2], vbq[2 * kPMax], dinv[kPMax];
   __shared__ int ord[kPMax], flags[2], posI[kPMax], posJ[kPMax], cnt[2], idxI[kPMax], idxJ[kPMax];
   const int t = threadIdx.x;
   const int nI = st->nIpre, nJ = st->nJpre;
@@ -717,7 +748,9 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   // ---- the core M = A^+ R_R^T (|J| <= |I|, A = Q(I,:)) or R_C (A^+)^T (A = Z(J,:))
   const bool branch = nJ <= nI;
   const int m0 = branch ? nI : nJ, k0 = branch ? nJ : nI;
+  const double* Rm = branch ? R_R : R_C;  // m0 x m0 upper triangular, ld pm
   gather_rows(branch ? a.Q0 : a.Q1, a.ldq, branch ? idxI : idxJ, m0, k0, B0);  // zero-padded
+  load_block(Rm, pm, m0, m0, B3);
   __syncthreads();
   small_qr(B0, m0, k0, tau, vbq);
   tri_inverse(B0, k0, B1, dinv);  // B1 = R^{-1}, zero-padded
@@ -729,17 +762,13 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
     // With A = Q(I,:) and R_m = R_R (|J| <= |I|) the core is M = A^+ R_m^T; with A = Z(J,:) and
     // R_m = R_C it is M = R_C (A^+)^T, i.e. M^T = A^+ R_m^T: the same product, stored
     // transposed. A^+ R_m^T = R^{-1} (H^T R_m^T)(0:k0, :), H the QR's reflectors.
-    const double* Rm = branch ? R_R : R_C;  // m0 x m0 upper triangular, ld pm
-    explicit_reflectors(B0, m0, k0);
-    load_block(Rm, pm, m0, m0, B3);
-    __syncthreads();
     for (int e = t; e < kPMax * kPMax; e += blockDim.x) {  // B2 = R_m^T, zero-padded
       const int i = e % kPMax, j = e / kPMax;
       B2[i + j * LDP] = (j <= i) ? B3[j + i * LDP] : 0.0;
     }
-    __syncthreads();
+    explicit_reflectors(B0, m0, k0);  // ends with the barrier for B2, too
     apply_reflectors(B0, tau, m0, k0, B2, m0, true);
-    lds_gemm(B1, B2, B3, k0, m0, !branch);  // k0 x m0 product: M, or M^T stored transposed
+    lds_gemm(B1, B2, B3, k0, m0, k0, !branch);  // k0 x m0 product: M, or M^T stored transposed
     __syncthreads();
     M = B3;
   } else {
@@ -748,9 +777,9 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
     set_identity(B1, k0);
     __syncthreads();
     JacProb pr{B0, m0, k0, B1};
-    jacobi(&pr, 1, flags);
-    norms_sorted(B0, m0, k0, sig, ord);
-    const double smax = sig[ord[0]];
+    jacobi_waves<true, 4, true>(pr, flags);
+    norms_sorted(B0, m0, k0, sig, ord, srt);
+    const double smax = srt[0];
     const double cut = cut_pinv * kEps * smax;
     for (int e = t; e < m0 * k0; e += blockDim.x) {  // U_c / s_c = X_c / s_c^2, dropped -> 0
       const int i = e % m0, c = e / m0;
@@ -797,15 +826,15 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   double* Ub = B2;
   double* Vb = B0;
   int sweeps = 0;
-  const int r = svd_qr(M, nJ, nI, cut_pinv, B0, B1, B2, tau, vbq, sig, ord, flags, &sweeps);
-  // now Ub = U^ (nJ x r), Vb = V~ (nI x r), singular values sig[ord[0..r)]
+  const int r = svd_qr(M, nJ, nI, cut_pinv, B0, B1, B2, tau, vbq, sig, ord, srt, flags, &sweeps);
+  // now Ub = U^ (nJ x r), Vb = V~ (nI x r), singular values srt[0..r)
   for (int e = t; e < r * pm; e += blockDim.x) {
     const int i = e % pm, rr = e / pm;
     a.Uhat[i + (int64_t)rr * pm] = i < nJ ? Ub[i + rr * LDP] : 0.0;
     a.Vtil[i + (int64_t)rr * pm] = i < nI ? Vb[i + rr * LDP] : 0.0;
   }
   const int nb = a.nb;
-  if (t < kPMax) st->S[nb][t] = t < r ? sig[ord[t]] : 0.0;
+  if (t < kPMax) st->S[nb][t] = t < r ? srt[t] : 0.0;
 
   // ---- pruning: wave 0 takes the diagonal of R_R, wave 1 that of R_C, one lane per index; the
   // kept indices are compacted in order through a ballot
@@ -827,12 +856,10 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   // k_eta after rho, and only when it can matter: rows of an orthonormal basis have singular
   // values <= 1, so eta_1, eta_2 >= 1 and the indicator is at least 2 S_min / ||S||_F; when that
   // bound already fails the test (or at pass 0, where no stop is allowed) no stop is possible.
-  bool need_eta;
-  {
-    double n2 = 0.0;
-    for (int l = 0; l < r; ++l) n2 = fma(sig[ord[l]], sig[ord[l]], n2);
-    need_eta = r > 0 && st->k >= 1 && nIp > 0 && nJp > 0 && 1.9 * sig[ord[r - 1]] < st->eps * sqrt(n2);
-  }
+  const double nrm = sqrt(sorted_norm2(srt, r));
+  const bool need_eta = r > 0 && st->k >= 1 && nIp > 0 && nJp > 0 && 1.9 * srt[max(r - 1, 0)] < st->eps * nrm;
+  const int lane = t & 63;
+  const int rs = __popcll(__ballot(lane < r && srt[lane] > st->eps * srt[0]));
   __syncthreads();
 
   // index sets of the new iterate, one thread per index
@@ -847,17 +874,12 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
     st->Jb[nb][t - kPMax] = v;
   }
   if (t == 0) {
-    double n2 = 0.0;
-    for (int l = 0; l < r; ++l) n2 = fma(sig[ord[l]], sig[ord[l]], n2);
-    const double nrm = sqrt(n2);
     st->nrm = nrm;
     st->eta1 = INFINITY;
     st->eta2 = INFINITY;
     st->ind = INFINITY;
     st->eta_need = need_eta ? 1 : 0;
     st->r[nb] = r;
-    int rs = 0;
-    for (int l = 0; l < r; ++l) rs += sig[ord[l]] > st->eps * sig[ord[0]] ? 1 : 0;
     st->r_sig = rs;
     st->nI = nIp;
     st->nJ = nJp;
@@ -910,15 +932,18 @@ __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
     gather_rows(q == 0 ? a.Q0 : a.Q1, a.ldq, idx, ns, kc, Qs);
     load_block(q == 0 ? a.Uhat : a.Vtil, a.pmax, kc, r, Us);
     __syncthreads();
-    lds_gemm(Qs, Us, E, ns, r, !tall);
+    zero_block(E);
     __syncthreads();
-    JacProb pp[1] = {{E, tall ? ns : r, tall ? r : ns, nullptr}};
-    jacobi(pp, 1, flags);
+    lds_gemm(Qs, Us, E, ns, r, kc, !tall);
+    __syncthreads();
+    const JacProb pr{E, tall ? ns : r, tall ? r : ns, nullptr};
+    jacobi<false>(pr, flags);
     if (t < 64) {  // smallest column norm
       double v = INFINITY;
-      if (t < pp[0].k) {
+      if (t < pr.k) {
         double s = 0.0;
-        for (int i = 0; i < pp[0].m; ++i) s = fma(E[i + t * LDP], E[i + t * LDP], s);
+#pragma unroll 8
+        for (int i = 0; i < pr.m; ++i) s = fma(E[i + t * LDP], E[i + t * LDP], s);
         v = sqrt(s);
       }
       for (int msk = 32; msk >= 1; msk >>= 1) v = fmin(v, shfl_xor_d(v, msk));
@@ -972,7 +997,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
   DevState* st = a.st;
   if (st->done) return;
   __shared__ double B0[kBuf], B1[kBuf], B2[kBuf], B3[kBuf];
-  __shared__ double sig[kPMax], tau[kPMax], vbq[2 * kPMax];
+  __shared__ double sig[kPMax], srt[kPMax], tau[kPMax], vbq[2 * kPMax];
   __shared__ int ord[kPMax], flags[2];
   const int t = threadIdx.x;
   // the width of the start: the right-hand side's rank, or the guess's columns
@@ -986,12 +1011,13 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
   for (int e = t; e < rF * rF; e += blockDim.x) {
     const int i = e % rF, j = e / rF;
     double s = 0.0;
+#pragma unroll 8
     for (int m = max(i, j); m < rF; ++m) s = fma(B0[i + m * LDP], B1[j + m * LDP], s);
     B3[i + j * LDP] = s;
   }
   __syncthreads();
   int sweeps = 0;
-  const int r = svd_qr(B3, rF, rF, (double)rF, B0, B1, B2, tau, vbq, sig, ord, flags, &sweeps);
+  const int r = svd_qr(B3, rF, rF, (double)rF, B0, B1, B2, tau, vbq, sig, ord, srt, flags, &sweeps);
   // a zero guess leaves the start from the right-hand side in place
   if (a.guess && r == 0) {
     if (t == 0) st->guess_ok = 0;
@@ -1002,8 +1028,9 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
     a.Uhat[i + (int64_t)rr * pm] = i < rF ? B2[i + rr * LDP] : 0.0;
     a.Vtil[i + (int64_t)rr * pm] = i < rF ? B0[i + rr * LDP] : 0.0;
   }
-  if (t < kPMax) st->S[0][t] = t < r ? sig[ord[t]] : 0.0;
-  __syncthreads();
+  if (t < kPMax) st->S[0][t] = t < r ? srt[t] : 0.0;
+  const int lane = t & 63;
+  const int rs = __popcll(__ballot(lane < r && srt[lane] > st->eps * srt[0]));
   if (t == 0 && a.guess) st->guess_ok = 1;
   if (t == 0) {
     st->r[0] = r;
@@ -1020,8 +1047,6 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
       st->status = LRP_OK;
       st->r_sig = 0;
     } else {
-      int rs = 0;
-      for (int l = 0; l < r; ++l) rs += st->S[0][l] > st->eps * st->S[0][0] ? 1 : 0;
       st->r_sig = rs;
     }
   }
