@@ -1137,31 +1137,43 @@ int scan_inputs_launch(DevState* st, const double* U, int64_t ldu, const double*
   return launch_status();
 }
 
-// r* = smallest r with sum_{l >= r} S_l^2 < (eps ||S||)^2 ; rank = max(min(r*, r_max), 1).
-__global__ void k_finalize(DevState* st, double* S_out, int r_max) {
-  if (threadIdx.x != 0) return;
+// r* = smallest r with sum_{l >= r} S_l^2 < (eps ||S||)^2 ; rank = max(min(r*, r_max), 1). One wave: the
+// singular values are loaded and stored by a lane each and summed in order from LDS (one thread
+// that waited on each load and store took 4 to 12 us, this 2.5 to 4.5).
+__global__ __launch_bounds__(64) void k_finalize(DevState* st, double* S_out, int r_max) {
   if (st->status < 0) return;
+  const int t = threadIdx.x;
+  const int b = st->ret, m = st->r[b];
+  const bool zero = st->zero != 0;
+  __shared__ double S[kPMax], sq[kPMax];
+  const double v = st->S[b][t];
+  S[t] = t < m ? v : 0.0;
+  sq[t] = 0.0;
+  __syncthreads();
   int rank = 1;
-  const int b = st->ret;
-  const double* S = st->S[b];
-  if (!st->zero) {
-    const int m = st->r[b];
-    double nrm2 = 0.0;
-    for (int l = 0; l < m; ++l) nrm2 = fma(S[l], S[l], nrm2);
+  if (!zero) {
+    const double nrm2 = sorted_norm2(S, m);
     const double thr = (st->eps * sqrt(nrm2)) * (st->eps * sqrt(nrm2));
+    // sq[rr] = sum_{l >= rr} S_l^2, summed from the end; r* is one past the last rr that is not below thr
     double tail = 0.0;
-    int rstar = m;
-    for (int rr = m; rr >= 0; --rr) {
-      if (rr < m) tail = fma(S[rr], S[rr], tail);
-      if (tail < thr)
-        rstar = rr;
-      else
-        break;
+    for (int r0 = (m + 7) & ~7; r0 > 0; r0 -= 8) {
+      double x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = S[r0 - 1 - u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        tail = fma(x[u], x[u], tail);
+        if (t == 0) sq[r0 - 1 - u] = tail;
+      }
     }
+    __syncthreads();
+    const unsigned long long above = __ballot(t < m && !(sq[t] < thr));
+    int rstar = 64 - __clzll((long long)above);
+    if (!(0.0 < thr)) rstar = m;  // not even the empty sum is below
     rank = max(min(rstar, r_max), 1);
   }
-  st->r_final = rank;
-  for (int l = 0; l < r_max; ++l) S_out[l] = (!st->zero && l < rank) ? S[l] : 0.0;
+  if (t == 0) st->r_final = rank;
+  if (t < r_max) S_out[t] = (!zero && t < rank) ? v : 0.0;
 }
 
 int finalize_launch(DevState* st, double* S_out, int r_max, hipStream_t s) {

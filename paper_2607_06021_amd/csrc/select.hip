@@ -7,8 +7,8 @@
 // A pass stops at a fixed point: when both new sets equal the previous pass's sets, the
 // cross approximation would repeat, and the previous iterate is the result.
 //
-// Kernels: k_pi (scores and per-block maxima), k_gmax (global maximum), k_topk_block
-// (the best 64 of each 256-row block, ranked by counting), k_topk_merge (16 sorted lists of
+// Kernels: k_pi (scores and per-block maxima), k_gmax (global maximum, where the blocks are many),
+// k_topk_block (the best 64 of each 256-row block, ranked by counting), k_topk_merge (16 sorted lists of
 // 64 per block merged pairwise, by rank, until one list is left), k_select (set update, fixed-point
 // test, trace).
 #include "lrp_kernels.h"
@@ -97,7 +97,9 @@ __global__ __launch_bounds__(256) void k_gmax(Src in) {
 struct TopkArgs {
   const DevState* st;
   const double* pi[2];
-  const double* gmax;
+  const double* gmax;     // per side, or null: the largest of the nb block maxima bmax
+  const double* bmax[2];
+  int nb;
   int64_t n;
   double* cs[2];  // out: nblocks x kPMax scores
   int* ci[2];
@@ -106,9 +108,28 @@ struct TopkArgs {
   uint64_t seed;
 };
 
+// Entries 2 q .. 2 q + 63 of es2 that come before an entry of score cs: those of a larger score, and,
+// where they stand before it in the block (TIES), of an equal one.
+template <bool TIES>
+__device__ __forceinline__ int count_before(const double2* es2, double cs) {
+  int rk = 0;
+#pragma unroll 8
+  for (int q = 0; q < 32; ++q) {
+    const double2 o = es2[q];
+    rk += TIES ? (o.x >= cs) + (o.y >= cs) : (o.x > cs) + (o.y > cs);
+  }
+  return rk;
+}
+
+// Up to here every block finds the largest score from the block maxima itself (nb / 256 loads per
+// thread, 1 us) and k_gmax's launch (4.5 us) is left out; at 4096 maxima the blocks would read 32 KB each.
+constexpr int kGmaxBlocks = 1024;
+
 // Rank of each entry of a 256-row block in the (score desc, index asc) order by counting the
-// entries before it; scores sit in their own LDS array and are read two per load (the same
-// address on every lane, a broadcast), indices only for a tied score.
+// entries before it, a broadcast read of two scores at a time. The indices ascend through the
+// block (the padding's, too), so an index is never compared: an equal score comes first where its
+// entry stands earlier, which only the wave's own 64 entries must look up. No branches: with one on each
+// tied pair the kernel took 16.5 us, now 6.5 with the maximum included (8.5 on 512 blocks).
 template <class Src>
 __global__ __launch_bounds__(256) void k_topk_block(Src in) {
   const TopkArgs& a = kernel_args<TopkArgs>(in);
@@ -116,14 +137,21 @@ __global__ __launch_bounds__(256) void k_topk_block(Src in) {
   if (st->done) return;
   const int side = blockIdx.y;
   __shared__ double2 es2[kSelRows / 2];
-  __shared__ int ei[kSelRows];
+  __shared__ double red[4];
   __shared__ __align__(16) int excl[kPMax];
   double* es = reinterpret_cast<double*>(es2);
   const int ne = side == 0 ? st->nI : st->nJ;
   const int* set = side == 0 ? st->I : st->J;
   if (threadIdx.x < kPMax) excl[threadIdx.x] = threadIdx.x < ne ? set[threadIdx.x] : -1;
   __syncthreads();
-  const double floor_v = kFloorRel * a.gmax[side];
+  double gm = 0.0;
+  if (a.gmax) {
+    gm = a.gmax[side];
+  } else {
+    for (int e = threadIdx.x; e < a.nb; e += kSelRows) gm = fmax(gm, a.bmax[side][e]);
+    gm = block_max256(gm, red);
+  }
+  const double floor_v = kFloorRel * gm;
   const int64_t i = (int64_t)blockIdx.x * kSelRows + threadIdx.x;
   double cs;
   int ci;
@@ -150,16 +178,19 @@ __global__ __launch_bounds__(256) void k_topk_block(Src in) {
     ci = 0x40000000 + (int)threadIdx.x;
   }
   es[threadIdx.x] = cs;
-  ei[threadIdx.x] = ci;
   __syncthreads();
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int rk = 0;
+#pragma unroll 1
+  for (int b = 0; b < w; ++b) rk += count_before<true>(es2 + 32 * b, cs);
 #pragma unroll 8
-  for (int q = 0; q < kSelRows / 2; ++q) {
-    const double2 o = es2[q];
-    rk += (o.x > cs) + (o.y > cs);
-    if (o.x == cs) rk += ei[2 * q] < ci;
-    if (o.y == cs) rk += ei[2 * q + 1] < ci;
+  for (int q = 0; q < 32; ++q) {  // the wave's own entries
+    const double2 o = es2[32 * w + q];
+    rk += (int)(o.x > cs) | ((int)(o.x == cs) & (int)(2 * q < lane));
+    rk += (int)(o.y > cs) | ((int)(o.y == cs) & (int)(2 * q + 1 < lane));
   }
+#pragma unroll 1
+  for (int b = w + 1; b < kSelRows / 64; ++b) rk += count_before<false>(es2 + 32 * b, cs);
   if (rk < kPMax) {
     a.cs[side][(int64_t)blockIdx.x * kPMax + rk] = cs;
     a.ci[side][(int64_t)blockIdx.x * kPMax + rk] = ci;
@@ -609,18 +640,24 @@ int select_candidates(const SelectPlan& p, const DevState* st, const double* U[2
     pa.bmax[q] = p.bmax[q];
   }
   LRP_LAUNCH_G(K_PI, k_pi<PiArgs>, k_pi<GroupRef>, dim3(p.nblocks, 2), dim3(256), 0, s, pa);
-  GmaxArgs ga{};
-  ga.st = st;
-  ga.b[0] = p.bmax[0];
-  ga.b[1] = p.bmax[1];
-  ga.nb = p.nblocks;
-  ga.gmax = p.gmax;
-  LRP_LAUNCH_G(K_GMAX, k_gmax<GmaxArgs>, k_gmax<GroupRef>, dim3(2), dim3(256), 0, s, ga);
+  const bool own_gmax = p.nblocks <= kGmaxBlocks;
+  if (!own_gmax) {
+    GmaxArgs ga{};
+    ga.st = st;
+    ga.b[0] = p.bmax[0];
+    ga.b[1] = p.bmax[1];
+    ga.nb = p.nblocks;
+    ga.gmax = p.gmax;
+    LRP_LAUNCH_G(K_GMAX, k_gmax<GmaxArgs>, k_gmax<GroupRef>, dim3(2), dim3(256), 0, s, ga);
+  }
   TopkArgs ta{};
   ta.st = st;
   ta.pi[0] = p.pi[0];
   ta.pi[1] = p.pi[1];
-  ta.gmax = p.gmax;
+  ta.gmax = own_gmax ? nullptr : p.gmax;
+  ta.bmax[0] = p.bmax[0];
+  ta.bmax[1] = p.bmax[1];
+  ta.nb = p.nblocks;
   ta.n = p.n;
   ta.sampled = so.sampled;
   ta.rho = so.rho;
