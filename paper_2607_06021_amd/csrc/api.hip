@@ -395,8 +395,6 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   ra.ldu = n;
   ra.nb_new = nb_new;
   ra.nb_old = nb_old;
-  ra.maxiter = c->maxiter;
-  ra.trace = c->trace;
   TRY(rho_launch(c->rho, ra, s));
   EtaArgs ea{};
   ea.st = c->st;
@@ -407,8 +405,11 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   ea.Vtil = c->Vtil;
   ea.pmax = pm;
   ea.nb = nb_new;
+  ea.M = c->rho.M;
+  ea.G = c->rho.G;
   ea.maxiter = c->maxiter;
   ea.trace = c->trace;
+  ea.stop = &c->done_host[k & 1];
   TRY(eta_launch(ea, s));
   return LRP_OK;
 }
@@ -696,29 +697,17 @@ int enqueue_pass(lrp_ctx* c, int k) {
 }
 
 // Pass k with the stop flag read between its two parts: the update part (captured per parity),
-// the flag copy and its event, then the candidate selection (captured per parity).
+// which ends by writing the flag, its event, then the candidate selection (captured per parity).
 int enqueue_pass_polled(lrp_ctx* c, int k) {
   TRY(enqueue_captured(c, k, &c->gexec_upd[graph_slot(c, k)], enqueue_pass_update));
   TRY(enqueue_poll(c, k));
   return enqueue_captured(c, k, &c->gexec_sel[k & 1], enqueue_pass_select);
 }
 
-// After pass k: copy the stop flag to pinned memory and mark the point with an event.
-// The stop flag into its pinned host slot. A one-thread kernel rather than a copy, so that the
-// pass boundary stays on the compute queue (a copy may go to a DMA engine, and the next pass
-// would wait for the hand-over between the two).
-__global__ void k_flag_copy(const int* src, int* dst) {
-  if (threadIdx.x == 0) {
-    *dst = *src;
-    __threadfence_system();
-  }
-}
-
+// After pass k, whose last workgroup wrote the stop flag to its pinned host slot: mark the point with an
+// event.
 int enqueue_poll(lrp_ctx* c, int k) {
-  const int slot = k & 1;
-  LRP_LAUNCH(K_COPY, k_flag_copy, dim3(1), dim3(64), 0, c->stream, &c->st->done, &c->done_host[slot]);
-  TRY(launch_status());
-  return hipEventRecord(c->evit[slot], c->stream) == hipSuccess ? LRP_OK : LRP_EDEVICE;
+  return hipEventRecord(c->evit[k & 1], c->stream) == hipSuccess ? LRP_OK : LRP_EDEVICE;
 }
 
 // Stage 3: final truncation, DST back into the caller's buffers, state read-back.
@@ -854,7 +843,7 @@ int solve_impl(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const double*
     TRY(enqueue_start(c, rF, U_F, ldu, sigma_F, V_F, ldv));
   else
     TRY(enqueue_start_matrix(c, rF, U_F, ldu, V_F, ldv));
-  // passes; the stop flag of pass k is copied right after its decision, and the host reads it
+  // passes; the stop flag of pass k is written with its decision, and the host reads it
   // while the device runs pass k's candidate selection, so no pass is enqueued after the stop
   // (only the selection of the last pass, whose kernels return at once)
   for (int k = 0; k < c->maxiter; ++k) {
@@ -979,7 +968,7 @@ int lrp_get_profile(const lrp_ctx* c, int32_t* count, lrp_kernel_time* out) {
       "k_init_state", "k_scan", "k_dst_single", "k_dst_pass1", "k_dst_pass2", "k_fiber",
       "k_tsqr_factor", "k_tsqr_apply", "k_core_warm", "k_core", "k_prod", "k_pi", "k_gmax",
       "k_topk_block", "k_topk_merge", "k_select", "k_rho_a", "k_rho_b", "k_rho_reduce",
-      "k_rho_final", "k_eta", "k_finalize", "copy", "empty kernel", "k_qdeim_step"};
+      "k_eta", "k_finalize", "copy", "empty kernel", "k_qdeim_step"};
   if (!c || !count || *count < 0 || (*count > 0 && !out)) return LRP_EINVAL;
   if (!c->profile || !c->solved) {
     *count = 0;

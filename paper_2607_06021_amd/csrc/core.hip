@@ -16,7 +16,7 @@
 //     min(eta_1 (1 + eta_2), eta_2 (1 + eta_1)) S_min / ||S||_F must pass for a stop; the
 //     indicator itself (eta_1 = 1/sigma_min(U_k(I,:)), eta_2 = 1/sigma_min(V_k(J,:)) on the
 //     pruned sets, two Jacobi problems solved side by side) and the stop decision are made by
-//     k_eta once rho is known, and only when a stop is possible.
+//     k_eta with rho, and only when a stop is possible.
 // The warm start uses the same SVD on M = R_u R_v^T, the core of F^ = U^ V^^T.
 //
 // Jacobi: Hestenes' one-sided method; a pair is rotated unless
@@ -903,25 +903,120 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   }
 }
 
-// Indicator and stop decision of a pass (Algorithm 4, after rho): when a stop is possible
-// (cheap bound passed, rho < eps), eta_1 = 1/sigma_min(U_k(I,:)) and eta_2 =
+// rho of a pass (see rho.hip) from M_u, N_v and the Gram matrices, by the whole workgroup: the three
+// 64 x 64 x 64 products run as 16 x 16 tiles on the matrix cores, the live tiles round the waves; every
+// matrix is zero past its live part. sh: 4 kBuf doubles, so: kPMax, red: 8 doubles of LDS.
+__device__ double rho_value(const EtaArgs& a, const DevState* st, double* sh, double* so, double* red) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = kEtaThreads / 64;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int r = st->r[a.nb], ro = st->r[a.nb ^ 1];
+  const double* S = st->S[a.nb];
+  double *Am = sh, *Nv = sh + kBuf, *Gu = sh + 2 * kBuf, *Gv = sh + 3 * kBuf;  // row-major, ld LDP
+  constexpr int kPer = kPMax * kPMax / kEtaThreads;  // 8
+  {
+    // the loads of a thread, all of one column, are in flight together
+    double vm[kPer], vn[kPer], vu[kPer], vv[kPer];
+    const double s = st->S[a.nb ^ 1][lane];
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+      const int e = t + kEtaThreads * m;
+      vm[m] = a.M[e];
+      vn[m] = a.M[kPMax * kPMax + e];
+      vu[m] = a.G[e];
+      vv[m] = a.G[kPMax * kPMax + e];
+    }
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+      const int o = (wave + nw * m) * LDP + lane;
+      Am[o] = vm[m] * s;  // M_u S'
+      Nv[o] = vn[m];
+      Gu[o] = vu[m];
+      Gv[o] = vv[m];
+    }
+    if (wave == 0) so[lane] = s;
+  }
+  __syncthreads();
+  const int nr = (r + 15) >> 4, no = (ro + 15) >> 4;
+  const int n1 = nr * nr, n2 = nr * no;
+  double part = 0.0;
+  for (int q = wave; q < n1 + 2 * n2; q += nw) {  // uniform per wave
+    const int kind = q < n1 ? 0 : q < n1 + n2 ? 1 : 2;
+    const int tile = kind == 0 ? q : kind == 1 ? q - n1 : q - n1 - n2;
+    const int w = kind == 0 ? nr : no, I = tile / w, J = tile % w;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    const int rowA = (16 * I + lr) * LDP + lk, rowB = (16 * J + lr) * LDP + lk, colB = lk * LDP + 16 * J + lr;
+    if (kind == 0) {  // S_k - M_u S' N_v^T
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[v] = (I == J && lk + 4 * v == lr && 16 * I + lr < r) ? S[16 * I + lr] : 0.0;
+      for (int k0 = 0; k0 < 16 * no; k0 += 16)
+#pragma unroll
+        for (int ks = 0; ks < 16; ks += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Am[rowA + k0 + ks], Nv[rowB + k0 + ks], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part = fma(acc[v], acc[v], part);
+    } else if (kind == 1) {  // tr(M_u S' G' S' M_u^T)
+      for (int k0 = 0; k0 < 16 * no; k0 += 16)
+#pragma unroll
+        for (int ks = 0; ks < 16; ks += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Am[rowA + k0 + ks], Gv[colB + (k0 + ks) * LDP], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part = fma(acc[v], Am[(16 * I + lk + 4 * v) * LDP + 16 * J + lr], part);
+    } else {  // tr(N_v S' G S' N_v^T)
+      for (int k0 = 0; k0 < 16 * no; k0 += 16)
+#pragma unroll
+        for (int ks = 0; ks < 16; ks += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Nv[rowA + k0 + ks] * so[lk + k0 + ks],
+                                                      Gu[colB + (k0 + ks) * LDP], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        part = fma(acc[v], Nv[(16 * I + lk + 4 * v) * LDP + 16 * J + lr] * so[16 * J + lr], part);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < kPer; ++m) {  // tr(S' G S' G')
+    const int i = wave + nw * m;
+    part += so[i] * Gu[i * LDP + lane] * so[lane] * Gv[lane * LDP + i];
+  }
+  part = wave_sum(part);
+  if (lane == 0) red[wave] = part;
+  __syncthreads();
+  double tot = 0.0;
+#pragma unroll
+  for (int w = 0; w < kEtaThreads / 64; ++w) tot += red[w];
+  __syncthreads();
+  return sqrt(fmax(tot, 0.0)) / st->nrm;
+}
+
+// rho, the indicator and the stop decision of a pass (Algorithm 4): both workgroups form rho where the
+// core's bound allows a stop (one launch less than a workgroup that did it for both, and the same
+// bits); when a stop is possible (rho < eps), eta_1 = 1/sigma_min(U_k(I,:)) and eta_2 =
 // 1/sigma_min(V_k(J,:)) on the pruned sets, with U_k(I,:) = Q(I,:) U^ and V_k(J,:) = Z(J,:) V~
 // each stored tall (rows >= cols) so that Jacobi gives its min(rows, cols) singular values.
 // Workgroup q solves problem q (two CUs; a problem's sweeps do not depend on the other's), and
 // the second workgroup to finish makes the decision: the pass is accepted as the new iterate and
-// the solve stops when max(rho, indicator) < eps, or after maxiter passes.
+// the solve stops when max(rho, indicator) < eps, or after maxiter passes. It also writes the stop
+// flag to the host, which had been a launch of its own.
 template <class Src>
 __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
   const EtaArgs& a = kernel_args<EtaArgs>(in);
   DevState* st = a.st;
-  if (st->done) return;
-  __shared__ double E[kBuf], Qs[kBuf], Us[kBuf];
-  __shared__ double red[1];
-  __shared__ int flags[2], idx[kPMax], last;
   const int t = threadIdx.x, q = blockIdx.x;
+  if (st->done) {
+    if (q == 0 && t == 0) {
+      *a.stop = 1;
+      __threadfence_system();
+    }
+    return;
+  }
+  __shared__ double sh[4 * kBuf];
+  __shared__ double so[kPMax], red[8];
+  __shared__ int flags[2], idx[kPMax], last;
+  double *E = sh, *Qs = sh + kBuf, *Us = sh + 2 * kBuf;
   const int nb = a.nb;
   const int r = st->r[nb];
-  const bool need = st->k >= 1 && st->eta_need && st->rho < st->eps;
+  double rho = INFINITY;
+  if (st->k >= 1 && st->eta_need) rho = rho_value(a, st, sh, so, red);
+  const bool need = st->k >= 1 && st->eta_need && rho < st->eps;
   if (need) {
     // side 0: rows I of Q (ncols[0] columns) times U^; side 1: rows J of Z (ncols[1]) times V~
     const int ns = q == 0 ? st->nI : st->nJ;
@@ -931,7 +1026,6 @@ __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
     __syncthreads();
     gather_rows(q == 0 ? a.Q0 : a.Q1, a.ldq, idx, ns, kc, Qs);
     load_block(q == 0 ? a.Uhat : a.Vtil, a.pmax, kc, r, Us);
-    __syncthreads();
     zero_block(E);
     __syncthreads();
     lds_gemm(Qs, Us, E, ns, r, kc, !tall);
@@ -947,10 +1041,8 @@ __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
         v = sqrt(s);
       }
       for (int msk = 32; msk >= 1; msk >>= 1) v = fmin(v, shfl_xor_d(v, msk));
-      if (t == 0) red[0] = v;
+      if (t == 0) st->smin[q] = v;
     }
-    __syncthreads();
-    if (t == 0) st->smin[q] = red[0];
   }
   // publish this workgroup's result, then count it; the second to arrive sees both
   __threadfence();
@@ -972,18 +1064,27 @@ __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
       st->eta2 = eta2;
       if (st->nrm > 0.0) ind = fmin(eta1 * (1.0 + eta2), eta2 * (1.0 + eta1)) * st->S[nb][r - 1] / st->nrm;
     }
+    st->rho = rho;
+    st->rhob[nb] = rho;
     st->ind = ind;
     st->indb[nb] = ind;
-    if (kp < a.maxiter) a.trace.ind[kp] = ind;
+    if (kp < a.maxiter) {
+      a.trace.rho[kp] = rho;
+      a.trace.ind[kp] = ind;
+    }
     st->ret = nb;
     st->k = kp + 1;
-    if (kp >= 1 && fmax(st->rho, ind) < st->eps) {
-      st->done = 1;
+    int done = 0;
+    if (kp >= 1 && fmax(rho, ind) < st->eps) {
+      done = 1;
       st->status = LRP_OK;
     } else if (kp == a.maxiter - 1) {
-      st->done = 1;
+      done = 1;
       st->status = LRP_NOT_CONVERGED;
     }
+    if (done) st->done = 1;
+    *a.stop = done;
+    __threadfence_system();
   }
 }
 

@@ -17,7 +17,7 @@ namespace lrp {
 enum KernelId {
   K_INIT, K_SCAN, K_DST_SINGLE, K_DST_PASS1, K_DST_PASS2, K_FIBER, K_TSQR_FACTOR, K_TSQR_APPLY,
   K_CORE_WARM, K_CORE, K_PROD, K_PI, K_GMAX, K_TOPK_BLOCK, K_TOPK_MERGE, K_SELECT, K_RHO_A,
-  K_RHO_B, K_RHO_REDUCE, K_RHO_FINAL, K_ETA, K_FINALIZE, K_COPY, K_EMPTY, K_QDEIM, K_COUNT
+  K_RHO_B, K_RHO_REDUCE, K_ETA, K_FINALIZE, K_COPY, K_EMPTY, K_QDEIM, K_COUNT
 };
 // Called right before a launch (or copy) on stream s: when this thread is recording a
 // profile on s, records an event that ends the previous entry and starts this one.
@@ -250,8 +250,11 @@ struct EtaArgs {
   const double* Vtil;
   int pmax;
   int nb;              // iterate buffer of this pass
+  const double* M;     // M_u, N_v of rho (row: new column, column: old column)
+  const double* G;     // its Gram matrices Y^T Y, Y'^T Y'
   int maxiter;
   TraceBuf trace;
+  int* stop;           // pinned host copy of the stop flag, written at the end of the pass
 };
 int eta_launch(const EtaArgs& a, hipStream_t s);
 
@@ -329,8 +332,6 @@ struct RhoArgs {
   const double* Uold[2];  // U_{k-1}, V_{k-1}
   int64_t ldu;
   int nb_new, nb_old;
-  int maxiter;
-  TraceBuf trace;
 };
 int rho_launch(const RhoPlan& p, const RhoArgs& a, hipStream_t s);
 

@@ -8,8 +8,9 @@
 //   ||S_k - M_u S' N_v^T||^2, tr(M_u S' G' S' M_u^T), tr(N_v S' G S' N_v^T), tr(S' G S' G'),
 // with G = Y^T Y and G' = Y'^T Y' Gram matrices of explicitly formed small numbers.
 // rho is only needed when the core's cheap bound on the indicator allows a stop (the decision
-// needs both), so the n-length kernels return at once otherwise; the indicator itself and the
-// decision follow in k_eta. All reductions have a fixed order.
+// needs both), so the n-length kernels return at once otherwise. The kernels here leave M_u, N_v and
+// the Gram matrices; rho, the indicator and the decision follow in k_eta. All reductions have a
+// fixed order.
 #include "lrp_kernels.h"
 
 namespace lrp {
@@ -27,6 +28,7 @@ struct RhoKArgs {
   int nb_new, nb_old;
   const double* M;     // M_u, N_v (for the second pass)
   double* part;
+  double* one;         // a single row block: where the second pass's kernel forms M_u, N_v itself; or null
 };
 
 // st->k is the index of the pass being computed (the decision kernel advances it).
@@ -93,21 +95,34 @@ __device__ inline void store_partial(double* out, int w, int lr, int lk, const d
 
 // Pass A: partial M = A^T B over the block's rows (output tiles: NT = ceil(ro/16) columns,
 // rows below r).
-template <int NT>
-__device__ __forceinline__ void rho_a_body(const RhoKArgs& a, int side, int r, int ro, double* As, double* Bs) {
+template <int NT, int CH>
+__device__ __forceinline__ void rho_a_body(const RhoKArgs& a, int side, int r, int ro, double* As, double* Bs,
+                                           double* out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
   d4 acc[4];
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) acc[nt] = d4{0.0, 0.0, 0.0, 0.0};
   const int64_t row0 = (int64_t)blockIdx.x * a.rows_per_block;
   const int64_t rend = min(a.n, row0 + a.rows_per_block);
-  for (int64_t r0 = row0; r0 < rend; r0 += kRhoChunk) {
-    stage2(As, a.A[side], r, Bs, a.B[side], ro, a.ldu, rend, r0);
+  for (int64_t r0 = row0; r0 < rend; r0 += CH) {
+    stage2<CH>(As, a.A[side], r, Bs, a.B[side], ro, a.ldu, rend, r0);
     __syncthreads();
-    if (16 * w < r) gram_chunk<NT>(As, Bs, w, lr, lk, acc);  // uniform per wave
+    if (16 * w < r) gram_chunk<NT, CH>(As, Bs, w, lr, lk, acc);  // uniform per wave
     __syncthreads();
   }
-  store_partial(a.part + ((int64_t)blockIdx.x * 2 + side) * kPMax * kPMax, w, lr, lk, acc);
+  store_partial(out, w, lr, lk, acc);
+}
+
+template <int CH>
+__device__ __forceinline__ void rho_a_nt(const RhoKArgs& a, int side, int r, int ro, double* As, double* Bs,
+                                         double* out) {
+  switch ((ro + 15) >> 4) {  // uniform
+    case 0:
+    case 1: rho_a_body<1, CH>(a, side, r, ro, As, Bs, out); break;
+    case 2: rho_a_body<2, CH>(a, side, r, ro, As, Bs, out); break;
+    case 3: rho_a_body<3, CH>(a, side, r, ro, As, Bs, out); break;
+    default: rho_a_body<4, CH>(a, side, r, ro, As, Bs, out); break;
+  }
 }
 
 template <class Src>
@@ -118,13 +133,7 @@ __global__ __launch_bounds__(kRhoThreads) void k_rho_a(Src in) {
   const int side = blockIdx.y;
   const int r = st->r[a.nb_new], ro = st->r[a.nb_old];
   __shared__ double As[kRhoChunk * kRS], Bs[kRhoChunk * kRS];
-  switch ((ro + 15) >> 4) {  // uniform
-    case 0:
-    case 1: rho_a_body<1>(a, side, r, ro, As, Bs); break;
-    case 2: rho_a_body<2>(a, side, r, ro, As, Bs); break;
-    case 3: rho_a_body<3>(a, side, r, ro, As, Bs); break;
-    default: rho_a_body<4>(a, side, r, ro, As, Bs); break;
-  }
+  rho_a_nt<kRhoChunk>(a, side, r, ro, As, Bs, a.part + ((int64_t)blockIdx.x * 2 + side) * kPMax * kPMax);
 }
 
 // Pass B: Y = B - A M (rows of the chunk, MFMA with M as the second operand), then partial
@@ -205,6 +214,11 @@ __global__ __launch_bounds__(kRhoThreads) void k_rho_b(Src in) {
   const int r = st->r[a.nb_new], ro = st->r[a.nb_old];
   __shared__ double As[kRhoChunkB * kRS], Bs[kRhoChunkB * kRS];
   __shared__ double Ms[kPMax * kRS];
+  if (a.one) {  // this workgroup's partial is all of M_u (N_v): written here, read back below
+    rho_a_nt<kRhoChunkB>(a, side, r, ro, As, Bs, a.one + (int64_t)side * kPMax * kPMax);
+    __threadfence_block();
+    __syncthreads();
+  }
   switch ((r + 15) >> 4) {  // uniform: 4-column steps of A in groups of four
     case 0:
     case 1: rho_b_nt<4>(a, side, r, ro, As, Bs, Ms); break;
@@ -225,169 +239,47 @@ struct RhoReduceArgs {
   int nb_rows, nb_cols;
 };
 
+// A workgroup takes one row of 64 entries. The blocks are summed as four interleaved sums, (0 + 1) +
+// (2 + 3), block b in sum b mod 4 (the last nblocks mod 16 in sum 0), one sum per wave: bound by the
+// latency of its rounds of loads, of which one wave per sum makes a quarter (256 blocks: 12 -> 5.5 us).
 template <class Src>
 __global__ __launch_bounds__(256) void k_rho_reduce(Src in) {
   const RhoReduceArgs& a = kernel_args<RhoReduceArgs>(in);
   const DevState* st = a.st;
-  const double* part = a.part;
   const int nblocks = a.nblocks;
-  double* out = a.out;
   const int nb_rows = a.nb_rows, nb_cols = a.nb_cols;
   if (!rho_needed(st)) return;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;  // 0 .. 2*4096
-  if (e >= 2 * kPMax * kPMax) return;
-  const int side = e / (kPMax * kPMax), q = e % (kPMax * kPMax);
-  if (q / kPMax >= st->r[nb_rows] || q % kPMax >= st->r[nb_cols]) {
-    out[e] = 0.0;
-    return;
+  const int side = blockIdx.x / kPMax, row = blockIdx.x % kPMax, col = threadIdx.x & 63, j = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * kPMax + col;
+  __shared__ double part[3][kPMax];
+  double sm = 0.0;
+  if (row < st->r[nb_rows] && col < st->r[nb_cols]) {
+    const double* src = a.part + ((int64_t)side * kPMax + row) * kPMax + col;
+    const int64_t stride = 2 * kPMax * kPMax;
+    const int full = nblocks & ~15;
+    int b = j;
+    for (; b + 60 < full; b += 64) {
+      double v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = src[(int64_t)(b + 4 * k) * stride];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sm += v[k];
+    }
+    for (; b < full; b += 16) {
+      double v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = src[(int64_t)(b + 4 * k) * stride];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sm += v[k];
+    }
+    if (j == 0) {
+#pragma unroll 4
+      for (b = full; b < nblocks; ++b) sm += src[(int64_t)b * stride];
+    }
   }
-  // 16 loads in flight per step, added into four partial sums in a fixed order
-  double sm[4] = {0.0, 0.0, 0.0, 0.0};
-  const double* src = part + (int64_t)side * kPMax * kPMax + q;
-  const int64_t stride = 2 * kPMax * kPMax;
-  int b = 0;
-  for (; b + 15 < nblocks; b += 16) {
-    double v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = src[(int64_t)(b + k) * stride];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sm[k & 3] += v[k];
-  }
-  for (; b < nblocks; ++b) sm[0] += src[(int64_t)b * stride];
-  out[e] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
-}
-
-struct RhoFinalArgs {
-  DevState* st;
-  const double* M;  // M_u, N_v   (row a: new column, col m: old column)
-  const double* G;  // G_u = Y^T Y, G_v = Y'^T Y'
-  int nb_new, nb_old;
-  int maxiter;
-  TraceBuf trace;
-};
-
-template <class Src>
-__global__ __launch_bounds__(256) void k_rho_final(Src in) {
-  const RhoFinalArgs& a = kernel_args<RhoFinalArgs>(in);
-  DevState* st = a.st;
-  if (st->done) return;
-  const bool need = rho_needed(st);
-  __shared__ double red[4];
-  // M_u S' and the small matrices N_v, G_u, G_v in LDS (the loops below read them at a
-  // data-dependent length, so from memory every read would wait on its own latency)
-  __shared__ double Am[kPMax][kPMax + 1], Nvs[kPMax][kPMax + 1], Gus[kPMax][kPMax + 1], Gvs[kPMax][kPMax + 1];
-  __shared__ double Sos[kPMax];
-  double rho = INFINITY;
-  if (need) {
-    const int r = st->r[a.nb_new], ro = st->r[a.nb_old];
-    const double* S = st->S[a.nb_new];
-    const double* So = Sos;
-    const double* Mu = a.M;
-    // every thread's loads are issued together (unrolled, fixed count), not one wait each
-    constexpr int kPer = kPMax * kPMax / 256;  // 16 (the kernel runs 256 threads)
-    if (threadIdx.x < kPMax) Sos[threadIdx.x] = st->S[a.nb_old][threadIdx.x];
-    {
-      double vn[kPer], vu[kPer], vv[kPer], vm[kPer];
-#pragma unroll
-      for (int m = 0; m < kPer; ++m) {
-        const int e = threadIdx.x + 256 * m;
-        vn[m] = a.M[kPMax * kPMax + e];
-        vu[m] = a.G[e];
-        vv[m] = a.G[kPMax * kPMax + e];
-        vm[m] = Mu[e];
-      }
-#pragma unroll
-      for (int m = 0; m < kPer; ++m) {
-        const int e = threadIdx.x + 256 * m, aa = e / kPMax, c = e % kPMax;
-        Nvs[aa][c] = vn[m];
-        Gus[aa][c] = vu[m];
-        Gvs[aa][c] = vv[m];
-        Am[aa][c] = vm[m];  // M_u for now; times S' below
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-      const int e = threadIdx.x + 256 * m, aa = e / kPMax, c = e % kPMax;
-      Am[aa][c] = (aa < r && c < ro) ? Am[aa][c] * So[c] : 0.0;  // M_u S'
-    }
-    __syncthreads();
-    // N_v S' (Bm) is formed where it is used, with the same rounding as a stored product
-    auto Bm = [&](int aa, int m) { return (aa < r && m < ro) ? Nvs[aa][m] * So[m] : 0.0; };
-    // T1 to T3 over 4 x 4 blocks of entries, thread t taking rows a0 .. a0+3 and columns
-    // c0 .. c0+3 (the 256 threads tile 64 x 64), so that every operand read from LDS serves four
-    // entries; each entry sums over m in increasing order.
-    double part = 0.0;
-    const int a0 = 4 * (threadIdx.x >> 4), c0 = 4 * (threadIdx.x & 15);
-    if (a0 < r && c0 < r) {  // T1: ||S_k - M_u S' N_v^T||^2
-      double sq[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sq[i][j] = (a0 + i == c0 + j && a0 + i < r) ? S[a0 + i] : 0.0;
-      for (int m = 0; m < ro; ++m) {
-        double am[4], nv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          am[i] = Am[a0 + i][m];
-          nv[i] = Nvs[c0 + i][m];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) sq[i][j] = fma(-am[i], nv[j], sq[i][j]);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (a0 + i < r && c0 + j < r) part = fma(sq[i][j], sq[i][j], part);
-    }
-    if (a0 < r && c0 < ro) {  // T2 and T3
-      double p2[4][4], p3[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p2[i][j] = p3[i][j] = 0.0;
-      for (int m = 0; m < ro; ++m) {
-        double am[4], bm[4], gv[4], gu[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          am[i] = Am[a0 + i][m];
-          bm[i] = Bm(a0 + i, m);
-          gv[i] = Gvs[m][c0 + i];
-          gu[i] = Gus[m][c0 + i];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            p2[i][j] = fma(am[i], gv[j], p2[i][j]);
-            p3[i][j] = fma(bm[i], gu[j], p3[i][j]);
-          }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (a0 + i < r && c0 + j < ro) {
-            part = fma(p2[i][j], Am[a0 + i][c0 + j], part);
-            part = fma(p3[i][j], Bm(a0 + i, c0 + j), part);
-          }
-    }
-    for (int e = threadIdx.x; e < ro * ro; e += blockDim.x) {  // T4
-      const int m = e / ro, m2 = e % ro;
-      part += So[m] * Gus[m][m2] * So[m2] * Gvs[m2][m];
-    }
-    const double tot = block_sum256(part, red);
-    rho = sqrt(fmax(tot, 0.0)) / st->nrm;
-  }
-  if (threadIdx.x == 0) {
-    const int kp = st->k;
-    st->rho = rho;
-    st->rhob[a.nb_new] = rho;
-    if (kp < a.maxiter) a.trace.rho[kp] = rho;
-  }
+  if (j > 0) part[j - 1][col] = sm;
+  __syncthreads();
+  if (j == 0) a.out[e] = (sm + part[0][col]) + (part[1][col] + part[2][col]);
 }
 
 int rho_plan(RhoPlan* p, int64_t n) {
@@ -417,25 +309,22 @@ int rho_launch(const RhoPlan& p, const RhoArgs& ra, hipStream_t s) {
   a.nb_new = ra.nb_new;
   a.nb_old = ra.nb_old;
   a.part = p.part;
-  const int red_blocks = (2 * kPMax * kPMax + 255) / 256;
+  if (p.nblocks == 1) {
+    // one row block (n <= 256): its partials are the sums, and one launch does what takes four
+    a.M = a.one = p.M;
+    a.part = p.G;
+    LRP_LAUNCH_G(K_RHO_B, k_rho_b<RhoKArgs>, k_rho_b<GroupRef>, dim3(1, 2), dim3(kRhoThreads), 0, s, a);
+    return launch_status();
+  }
   LRP_LAUNCH_G(K_RHO_A, k_rho_a<RhoKArgs>, k_rho_a<GroupRef>, dim3(p.nblocks, 2), dim3(kRhoThreads), 0, s, a);
   const RhoReduceArgs rd{ra.st, p.part, p.nblocks, p.M, ra.nb_new, ra.nb_old};
-  LRP_LAUNCH_G(K_RHO_REDUCE, k_rho_reduce<RhoReduceArgs>, k_rho_reduce<GroupRef>, dim3(red_blocks), dim3(256), 0, s,
+  LRP_LAUNCH_G(K_RHO_REDUCE, k_rho_reduce<RhoReduceArgs>, k_rho_reduce<GroupRef>, dim3(2 * kPMax), dim3(256), 0, s,
                rd);
   a.M = p.M;
   LRP_LAUNCH_G(K_RHO_B, k_rho_b<RhoKArgs>, k_rho_b<GroupRef>, dim3(p.nblocks, 2), dim3(kRhoThreads), 0, s, a);
   const RhoReduceArgs rg{ra.st, p.part, p.nblocks, p.G, ra.nb_old, ra.nb_old};
-  LRP_LAUNCH_G(K_RHO_REDUCE, k_rho_reduce<RhoReduceArgs>, k_rho_reduce<GroupRef>, dim3(red_blocks), dim3(256), 0, s,
+  LRP_LAUNCH_G(K_RHO_REDUCE, k_rho_reduce<RhoReduceArgs>, k_rho_reduce<GroupRef>, dim3(2 * kPMax), dim3(256), 0, s,
                rg);
-  RhoFinalArgs f{};
-  f.st = ra.st;
-  f.M = p.M;
-  f.G = p.G;
-  f.nb_new = ra.nb_new;
-  f.nb_old = ra.nb_old;
-  f.maxiter = ra.maxiter;
-  f.trace = ra.trace;
-  LRP_LAUNCH_G(K_RHO_FINAL, k_rho_final<RhoFinalArgs>, k_rho_final<GroupRef>, dim3(1), dim3(256), 0, s, f);
   return launch_status();
 }
 

@@ -90,39 +90,21 @@ struct Group {
   std::vector<LaunchRec> recs;
   size_t area = 0;                    // bytes of one parity's argument blocks
   hipStream_t stream = nullptr;
-  const char** table = nullptr;       // device: kTable entries (see GroupTable)
+  const char** table = nullptr;       // device: kMaxGroup entries (see GroupTable)
   hipGraphExec_t exec[kMaxGroup] = {};  // by group size - 1, captured on first use
   bool broken = false;                // a graph could not be built: passes run per slot
 };
 
 // The table of one grouped launch, per request z of the group: the base of its argument blocks
-// (the GroupRef bases), its device stop flag and the pinned host slot the flag is copied to.
+// (the GroupRef bases).
 struct GroupTable {
   const char* base[kMaxGroup];
-  const int* src[kMaxGroup];
-  int* dst[kMaxGroup];
 };
-constexpr int kTable = 3 * kMaxGroup;
 
 // The table of the group's next launch (written on the group's stream before its graph).
 __global__ void k_group_table(const char** table, GroupTable g, int count) {
   const int t = threadIdx.x;
-  if (t < count) {
-    table[t] = g.base[t];
-    table[kMaxGroup + t] = reinterpret_cast<const char*>(g.src[t]);
-    table[2 * kMaxGroup + t] = reinterpret_cast<const char*>(g.dst[t]);
-  }
-}
-
-// The last node of a grouped pass: each request's stop flag into its pinned host slot.
-__global__ void k_group_poll(const char* const* table, int count) {
-  const int t = threadIdx.x;
-  if (t < count) {
-    const int* src = reinterpret_cast<const int*>(table[kMaxGroup + t]);
-    int* dst = reinterpret_cast<int*>(const_cast<char*>(table[2 * kMaxGroup + t]));
-    *dst = *src;
-  }
-  __threadfence_system();
+  if (t < count) table[t] = g.base[t];
 }
 
 }  // namespace
@@ -207,7 +189,7 @@ void setup_group(lrp_server* s, Slot& sl) {
     G.recs = r0.recs;
     G.area = half;
     ok = hipStreamCreateWithFlags(&G.stream, hipStreamNonBlocking) == hipSuccess;
-    if (ok && hipMalloc((void**)&G.table, sizeof(char*) * kTable) != hipSuccess) {
+    if (ok && hipMalloc((void**)&G.table, sizeof(char*) * kMaxGroup) != hipSuccess) {
       (void)hipStreamDestroy(G.stream);
       ok = false;
     }
@@ -228,7 +210,7 @@ void setup_group(lrp_server* s, Slot& sl) {
 }
 
 // The graph of one grouped pass of m requests: the recorded launches with grid z = m, each
-// kernel reading its argument block through the group's table, then the stop-flag copies.
+// kernel reading its argument block through the group's table.
 int build_group_graph(Group& G, int m, hipGraphExec_t* out) {
   hipGraph_t gr = nullptr;
   if (hipStreamBeginCapture(G.stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
@@ -244,10 +226,6 @@ int build_group_graph(Group& G, int m, hipGraphExec_t* out) {
       break;
     }
   }
-  if (ok) {
-    hipLaunchKernelGGL(k_group_poll, dim3(1), dim3(kMaxGroup), 0, G.stream, G.table, m);
-    ok = hipGetLastError() == hipSuccess;
-  }
   ok = (hipStreamEndCapture(G.stream, &gr) == hipSuccess) && ok;
   if (ok) ok = hipGraphInstantiate(out, gr, nullptr, nullptr, 0) == hipSuccess;
   if (gr) (void)hipGraphDestroy(gr);
@@ -259,8 +237,8 @@ int build_group_graph(Group& G, int m, hipGraphExec_t* out) {
   return LRP_OK;
 }
 
-// One grouped pass of the m slots in mem (each at its own pass index): the table, the graph
-// (whose last node copies the stop flags to the host) and each slot's pass event. LRP_EINVAL: no graph (nothing
+// One grouped pass of the m slots in mem (each at its own pass index): the table, the graph and each
+// slot's pass event. LRP_EINVAL: no graph (nothing
 // enqueued); LRP_EDEVICE: a launch failed.
 int launch_group(lrp_server* s, Group& G, Slot* const* mem, int m) {
   hipGraphExec_t& ex = G.exec[m - 1];
@@ -276,8 +254,6 @@ int launch_group(lrp_server* s, Group& G, Slot* const* mem, int m) {
   for (int i = 0; i < m; ++i) {
     const Slot& sl = *mem[i];
     gt.base[i] = sl.area + (size_t)(sl.k & 1) * G.area;
-    gt.src[i] = &sl.ctx->st->done;
-    gt.dst[i] = &sl.ctx->done_host[sl.k & 1];
   }
   hipLaunchKernelGGL(k_group_table, dim3(1), dim3(kMaxGroup), 0, G.stream, G.table, gt, m);
   if (hipGetLastError() != hipSuccess) return LRP_EDEVICE;
@@ -296,7 +272,7 @@ int launch_group(lrp_server* s, Group& G, Slot* const* mem, int m) {
 }
 
 // The slot's next pass on its own stream (after its previous pass if that ran on the group's
-// stream), with the stop-flag copy and its event.
+// stream), and its event.
 int solo_pass(lrp_server* s, Slot& sl) {
   lrp_ctx* c = sl.ctx;
   if (sl.moved) {

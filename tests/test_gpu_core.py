@@ -5,6 +5,7 @@ right-hand side has 64 random columns, so every sampled core is full and far fro
 import numpy as np
 import pytest
 
+import workloads
 from oracle import crossdeim as cd
 from test_gpu_solve import compare_fp64, gpu_solve
 
@@ -29,3 +30,15 @@ def test_core_sizes(nI, nJ):
     print(f"core {nI} x {nJ}", flush=True)
     o = cd.solve(n, U, s, V, 64, 1e-10, 1, replay=replay)
     compare_fp64(gpu_solve(n, U, s, V, 64, 1e-10, 1, replay=replay), o, f"core {nI}x{nJ}")
+
+
+@pytest.mark.parametrize("n", [256, 257, 4097, 16641])
+def test_rho_row_blocks(n):
+    """rho, the indicator and the stop at 1, 2, 17 and 66 row blocks of 256 (one launch; sums with a
+    remainder of 16 and of 64 blocks), against the oracle's values of every pass."""
+    U, s, V = workloads.make(workloads.CONFIGS["n4095_r10_fp64"], 0, n=n)
+    print(f"rho n={n}", flush=True)
+    o = cd.solve(n, U, s, V, 32, 1e-10, 20)
+    g = gpu_solve(n, U, s, V, 32, 1e-10, 20)
+    assert any(np.isfinite(t["rho"]) for t in g["trace"])
+    compare_fp64(g, o, f"rho n={n}")
