@@ -454,20 +454,12 @@ int enqueue_guess(lrp_ctx* c) {
   TRY(guess_begin_launch(c->st, r0, s));
   DstArgs da{};
   da.st = c->st;
-  da.X = c->guess_U;
-  da.ldx = c->guess_ldu;
+  da.nsides = 2;
   da.ncols = r0;
   da.ncols_out = r0;
-  da.Y = c->Uit[1];
-  da.ldy = n;
   da.full_bluestein = keep_rounding(c);
-  da.scale = c->guess_S;
-  da.outscale = 1.0;
-  TRY(dst_launch(c->dst, da, false, s));
-  da.X = c->guess_V;
-  da.ldx = c->guess_ldv;
-  da.Y = c->Vit[1];
-  da.scale = nullptr;
+  da.side[0] = DstSide{c->guess_U, nullptr, c->guess_ldu, c->Uit[1], nullptr, n, c->guess_S, 1.0};
+  da.side[1] = DstSide{c->guess_V, nullptr, c->guess_ldv, c->Vit[1], nullptr, n, nullptr, 1.0};
   TRY(dst_launch(c->dst, da, false, s));
   TsqrIO io{};
   io.st = c->st;
@@ -527,30 +519,13 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   TRY(scan_inputs_launch(c->st, U_F, ldu, V_F, ldv, sigma_F, n, rF, s));
   // spectral factors U^ = DST(U_F) diag(h^2 sigma), V^ = DST(V_F)
   DstArgs da{};
-  da.X = U_F;
-  da.ldx = ldu;
+  da.st = c->st;
+  da.nsides = 2;
   da.ncols = rF;
   da.ncols_out = rF;
-  da.ldy = n;
-  da.st = c->st;
-  da.scale = sigma_F;
   da.full_bluestein = keep_rounding(c);
-  da.outscale = h * h;
-  if (mixed)
-    da.Yf = c->Uh32;
-  else
-    da.Y = c->Uh;
-  TRY(dst_launch(c->dst, da, mixed, s));
-  da.X = V_F;
-  da.ldx = ldv;
-  da.scale = nullptr;
-  da.outscale = 1.0;
-  da.Y = nullptr;
-  da.Yf = nullptr;
-  if (mixed)
-    da.Yf = c->Vh32;
-  else
-    da.Y = c->Vh;
+  da.side[0] = DstSide{U_F, nullptr, ldu, mixed ? nullptr : c->Uh, mixed ? c->Uh32 : nullptr, n, sigma_F, h * h};
+  da.side[1] = DstSide{V_F, nullptr, ldv, mixed ? nullptr : c->Vh, mixed ? c->Vh32 : nullptr, n, nullptr, 1.0};
   TRY(dst_launch(c->dst, da, mixed, s));
   // warm start
   TsqrIO io{};
@@ -720,19 +695,11 @@ int enqueue_finish(lrp_ctx* c, double* U_out, int64_t ldou, double* S_out, doubl
   DstArgs db{};
   db.st = c->st;
   db.pick_ret = 1;
-  db.X = c->Uit[0];
-  db.X1 = c->Uit[1];
-  db.ldx = n;
-  db.Y = U_out;
-  db.ldy = ldou;
+  db.nsides = 2;
   db.ncols = 0;
   db.ncols_out = pm;
-  db.outscale = 1.0;
-  TRY(dst_launch(c->dst, db, mixed, s));
-  db.X = c->Vit[0];
-  db.X1 = c->Vit[1];
-  db.Y = V_out;
-  db.ldy = ldov;
+  db.side[0] = DstSide{c->Uit[0], c->Uit[1], n, U_out, nullptr, ldou, nullptr, 1.0};
+  db.side[1] = DstSide{c->Vit[0], c->Vit[1], n, V_out, nullptr, ldov, nullptr, 1.0};
   TRY(dst_launch(c->dst, db, mixed, s));
   if (hipEventRecord(c->ev1, s) != hipSuccess) return LRP_EDEVICE;
   prof_begin(s, K_COPY);
@@ -1099,14 +1066,10 @@ int lrp_dst1(lrp_ctx* c, int32_t ncols, const double* X, int64_t ldx, double* Y,
   if (precision != LRP_FP64 && precision != LRP_MIXED) return LRP_EINVAL;
   if (overlap(span(X, c->n, ldx, ncols, 8), span(Y, c->n, ldy, ncols, 8))) return LRP_EINVAL;
   DstArgs a{};
-  a.X = X;
-  a.ldx = ldx;
-  a.Y = Y;
-  a.ldy = ldy;
+  a.nsides = 1;
   a.ncols = ncols;
   a.ncols_out = ncols;
-  a.scale = scale;
-  a.outscale = mul;
+  a.side[0] = DstSide{X, nullptr, ldx, Y, nullptr, ldy, scale, mul};
   return dst_launch(c->dst, a, precision == LRP_MIXED, c->stream);
 }
 

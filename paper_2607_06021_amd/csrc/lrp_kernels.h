@@ -129,17 +129,21 @@ struct DstPlan {
   void* work2;             // batch_pairs x M complex: the data between the two FFTs (FP64 size)
 };
 
-struct DstArgs {
+struct DstSide {
   const double* X;   // source columns (ld ldx)
   const double* X1;  // second candidate source (pick_ret)
   int64_t ldx;
   double* Y;         // FP64 destination (ld ldy), or
   float* Yf;         // FP32 destination
   int64_t ldy;
-  int ncols;         // columns to transform
-  int ncols_out;     // columns written (extra ones are zero-filled)
   const double* scale;  // per-column factor or null
   double outscale;      // global factor (the launcher folds in 1/sqrt(2N))
+};
+struct DstArgs {
+  DstSide side[2];   // one or two sets of ncols columns; workgroup y takes set y
+  int nsides;
+  int ncols;         // columns to transform
+  int ncols_out;     // columns written (extra ones are zero-filled)
   const DevState* st;   // optional: skip after an error; pick_ret selects source/rank
   int pick_ret;
   int full_bluestein;   // 1: general n by full-length FFTs instead of the odd half (four-step sizes)
