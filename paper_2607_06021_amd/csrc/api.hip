@@ -120,12 +120,8 @@ void free_ctx(lrp_ctx* c) {
   if (c->evfin) (void)hipEventDestroy(c->evfin);
   for (int s = 0; s < 2; ++s)
     if (c->evit[s]) (void)hipEventDestroy(c->evit[s]);
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 4; ++s)
     if (c->gexec[s]) (void)hipGraphExecDestroy(c->gexec[s]);
-    if (c->gexec_upd[s]) (void)hipGraphExecDestroy(c->gexec_upd[s]);
-  }
-  for (int s = 0; s < 2; ++s)
-    if (c->gexec_sel[s]) (void)hipGraphExecDestroy(c->gexec_sel[s]);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -671,16 +667,7 @@ int enqueue_pass(lrp_ctx* c, int k) {
   return enqueue_captured(c, k, &c->gexec[graph_slot(c, k)], enqueue_pass_kernels);
 }
 
-// Pass k with the stop flag read between its two parts: the update part (captured per parity),
-// which ends by writing the flag, its event, then the candidate selection (captured per parity).
-int enqueue_pass_polled(lrp_ctx* c, int k) {
-  TRY(enqueue_captured(c, k, &c->gexec_upd[graph_slot(c, k)], enqueue_pass_update));
-  TRY(enqueue_poll(c, k));
-  return enqueue_captured(c, k, &c->gexec_sel[k & 1], enqueue_pass_select);
-}
-
-// After pass k, whose last workgroup wrote the stop flag to its pinned host slot: mark the point with an
-// event.
+// After pass k, whose decision wrote the stop flag to its pinned host slot: mark the point with an event.
 int enqueue_poll(lrp_ctx* c, int k) {
   return hipEventRecord(c->evit[k & 1], c->stream) == hipSuccess ? LRP_OK : LRP_EDEVICE;
 }
@@ -784,6 +771,21 @@ int64_t context_bytes(int64_t n, int pm, int maxiter, bool mixed) {
   return b;
 }
 
+// Waits until the device has written *flag (not negative any more). The pass's event, after its last
+// kernel, ends the wait where the flag does not come: the launches failed. Waiting for an event before
+// the selection instead split the pass in two graphs, 13 us apart (n = 255: 491 us per solve, 461 now).
+static int wait_flag(const volatile int* flag, hipEvent_t ev) {
+  for (int spin = 1; *flag < 0; ++spin) {
+    __builtin_ia32_pause();
+    if (spin & 255) continue;
+    const hipError_t e = hipEventQuery(ev);
+    if (e == hipSuccess) return *flag < 0 ? LRP_EDEVICE : LRP_OK;
+    if (e != hipErrorNotReady) return LRP_EDEVICE;
+    (void)hipGetLastError();  // not ready is not an error; leave no error state behind
+  }
+  return LRP_OK;
+}
+
 int solve_impl(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const double* sigma_F,
                const double* V_F, int64_t ldv, double* U_out, int64_t ldou, double* S_out,
                double* V_out, int64_t ldov, int32_t* r_out, lrp_info* info) {
@@ -810,13 +812,16 @@ int solve_impl(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const double*
     TRY(enqueue_start(c, rF, U_F, ldu, sigma_F, V_F, ldv));
   else
     TRY(enqueue_start_matrix(c, rF, U_F, ldu, V_F, ldv));
-  // passes; the stop flag of pass k is written with its decision, and the host reads it
-  // while the device runs pass k's candidate selection, so no pass is enqueued after the stop
-  // (only the selection of the last pass, whose kernels return at once)
+  // passes; the stop flag of pass k is written with its decision, in the middle of the pass's graph, and
+  // the host reads it while the device runs pass k's candidate selection, so no pass is enqueued after
+  // the stop (only the selection of the last pass, whose kernels return at once)
   for (int k = 0; k < c->maxiter; ++k) {
-    TRY(enqueue_pass_polled(c, k));
-    if (hipEventSynchronize(c->evit[k & 1]) != hipSuccess) return LRP_EDEVICE;
-    if (c->done_host[k & 1]) break;
+    volatile int* flag = &c->done_host[k & 1];
+    *flag = -1;  // pass k - 2, the slot's last writer, is over
+    TRY(enqueue_pass(c, k));
+    TRY(enqueue_poll(c, k));
+    TRY(wait_flag(flag, c->evit[k & 1]));
+    if (*flag) break;
   }
   if (c->matrix == LRP_MAT_POISSON)
     TRY(enqueue_finish(c, U_out, ldou, S_out, V_out, ldov));
