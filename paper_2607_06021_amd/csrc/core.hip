@@ -109,32 +109,57 @@ __device__ inline int jac_groups(int k) {
 // 4 g + j + 16 u, u < U, of the slot's two columns (a, b) and of their V columns; the odd slots run
 // their quads backwards (j = 3 - lane % 4). Rows past m (or k for V) are zero, and so is an empty
 // column, which is never rotated (its dot products vanish). In this layout
-//   * a dot product sums a quad by two DPP steps and the four lane rows by one MFMA (4 x 4 x 4, a
-//     row of ones: 29 cycles, where two more DPP or swap steps take 67);
+//   * a dot product is summed over the slot by two MFMAs (4 x 4 x 4, see slot_sum) and no lane moves;
 //   * the second columns change slots by one DPP move per 32 bits: slot ^ 1 is the mirror of each
 //     octet (the backward quads make its lanes meet their own rows), slot ^ 2 the lane row turned
 //     by 8. The cross-lane permutes through LDS that they replace waited 60 cycles each.
-// U = ceil(m / 16): a lone wave is bound by its instruction count here (a 16-row problem on 64-row
-// code took as long per step as a 64-row one, 1100 cycles).
+// U = ceil(m / 16): on 64-row code a 16-row problem took as long per step as a 64-row one.
 constexpr double kJacQuiet2 = 1e-16;  // (1e-8)^2: a rotation below this leaves the next sweep idle
 constexpr int kSlot1 = 0x141;         // row_half_mirror: the lane of slot ^ 1
 constexpr int kSlot2 = 0x128;         // row_ror:8: the lane of slot ^ 2
 
-// Sum over a slot's lanes. EXACT: the lane rows are added pairwise, (0 + 1) + (2 + 3), with the
-// rounding that the pseudo-inverse's callers rely on; otherwise in the matrix core's order.
+// Sum over a slot's lanes, on every lane of it. EXACT: pairwise by lane moves, (0 + 1) + (2 + 3) in the
+// quads and then the lane rows, with the rounding that the pseudo-inverse's callers rely on.
+// Otherwise by two products of v_mfma_f64_4x4x4 (A lane l = row l % 4 of block l / 4 % 4, inner index l / 16;
+// B lane l = column l % 4, inner index l / 16; result lane l = row l / 16, column l % 4; a block is a
+// slot): with x as A against ones the result's row i, on lane row i, is the sum of the quads' lanes i over
+// the lane rows, and with that as B against ones every entry is the sum of the four.
 template <bool EXACT>
 __device__ __forceinline__ double slot_sum(double x) {
+  if (!EXACT) {
+    x = __builtin_amdgcn_mfma_f64_4x4x4f64(x, 1.0, 0.0, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, x, 0.0, 0, 0, 0);
+  }
   x += dpp_move<0xB1>(x);  // quad_perm [1,0,3,2]
   x += dpp_move<0x4E>(x);  // quad_perm [2,3,0,1]
-  if (!EXACT) return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, x, 0.0, 0, 0, 0);
   const int lane = threadIdx.x & 63;
   x += lane_fetch(x, lane ^ 16);
   return x + lane_fetch(x, lane ^ 32);
 }
 
-template <bool WV, int U, bool EXACT>
-__device__ __forceinline__ void jac_pair(double (&a)[U], double (&b)[U], double (&va)[U], double (&vb)[U],
-                                         double tol2, bool& loud) {
+// 1 / sqrt(x) as rsq_nr with one step of third order (y (1 + e / 2 + 3 e^2 / 8), e = 1 - x y^2: the hardware
+// estimate's 2^-24 becomes 2^-70 before rounding) in place of two of second: four dependent
+// operations for six.
+__device__ __forceinline__ double rsq_h(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(fma(e, 0.375, 0.5), e * y, y);
+}
+
+// x, y <- c x - s y, s x + c y.
+template <int U>
+__device__ __forceinline__ void jac_rotate(double (&a)[U], double (&b)[U], double c, double sn) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const double x = a[u], y = b[u];
+    a[u] = c * x - sn * y;
+    b[u] = sn * x + c * y;
+  }
+}
+
+// Orthogonalizes the slots' column pairs; returns the rotations (c, s) (1, 0 where none was made).
+template <int U, bool EXACT>
+__device__ __forceinline__ double2 jac_pair(double (&a)[U], double (&b)[U], double tol2, bool& loud) {
   double al = 0.0, be = 0.0, ga = 0.0;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -148,86 +173,129 @@ __device__ __forceinline__ void jac_pair(double (&a)[U], double (&b)[U], double 
   const bool rot = ga != 0.0 && ga * ga > tol2 * al * be;
   loud |= rot && ga * ga > kJacQuiet2 * al * be;
   // Straight-line rotation for every slot (slots that do not rotate take c = 1, s = 0, which
-  // leaves the values of their columns unchanged); the extreme-range formula is out of line.
+  // leaves the values of their columns unchanged); the extreme-range formula is out of line. With
+  // y = 1 / h, h^2 = d^2 + 4ga^2: c^2 = (h + |d|) / (2h) = w and s = sign(d) ga / (h c) (the root of
+  // jacobi_rotation), so that c^2 + s^2 = w + (1 - w).
   const double d = be - al, g2 = 2.0 * ga;
   const double h2 = fma(d, d, g2 * g2);
-  const double h = h2 * rsq_nr(h2);
-  const double uu = h + fabs(d);
-  const double rr = rsq_nr(2.0 * h * uu);
-  double c = uu * rr, sn = copysign(1.0, d) * g2 * rr;
+  double c, sn;
+  if (EXACT) {
+    const double h = h2 * rsq_nr(h2);
+    const double uu = h + fabs(d);
+    const double rr = rsq_nr(2.0 * h * uu);
+    c = uu * rr;
+    sn = copysign(1.0, d) * g2 * rr;
+  } else {
+    const double y = rsq_h(h2);
+    const double w = fma(0.5 * fabs(d), y, 0.5);
+    const double rw = rsq_h(w);
+    c = w * rw;
+    sn = copysign(ga, d * ga) * y * rw;
+  }
   const bool rare = rot && !(h2 > 1e-290 && h2 < 1e290);
   if (__builtin_expect(__ballot(rare) != 0, 0)) {
     if (rare) jacobi_rotation(al, be, ga, c, sn);
   }
   c = rot ? c : 1.0;
   sn = rot ? sn : 0.0;
+  jac_rotate<U>(a, b, c, sn);
+  return make_double2(c, sn);
+}
+
+// The second columns of every slot move to slot ^ 1 or slot ^ 2.
+template <int U, int CTRL>
+__device__ __forceinline__ void jac_move_b(double (&b)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) b[u] = dpp_move<CTRL>(b[u]);
+}
+
+// Even slots take their odd neighbour's a as b, odd slots their even neighbour's b as a.
+template <int U>
+__device__ __forceinline__ void jac_swap_ab(double (&a)[U], double (&b)[U], bool odd) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const double x = a[u], y = b[u];
-    a[u] = c * x - sn * y;
-    b[u] = sn * x + c * y;
-  }
-  if (WV) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const double x = va[u], y = vb[u];
-      va[u] = c * x - sn * y;
-      vb[u] = sn * x + c * y;
-    }
+    const double x = dpp_move<kSlot1>(odd ? a[u] : b[u]);
+    a[u] = odd ? x : a[u];
+    b[u] = odd ? b[u] : x;
   }
 }
 
-// The second columns of every slot (and their V columns) move to slot ^ 1 or slot ^ 2.
-template <bool WV, int U, int CTRL>
-__device__ __forceinline__ void jac_move_b(double (&b)[U], double (&vb)[U]) {
+// A column from LDS and back; p: its and the lane's place. Every address lies in a 64 x LDP buffer,
+// whose entries past the problem are zero and stay so.
+template <int U>
+__device__ __forceinline__ void jac_load(const double* p, double (&x)[U]) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    b[u] = dpp_move<CTRL>(b[u]);
-    if (WV) vb[u] = dpp_move<CTRL>(vb[u]);
+  for (int u = 0; u < U; ++u) x[u] = p[16 * u];
+}
+template <int U>
+__device__ __forceinline__ void jac_store(double* p, const double (&x)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) p[16 * u] = x[u];
+}
+
+// One round of a wave's schedule over the columns of X. Rounds r < NG - 1: the circle schedule's group
+// pair (g, h) of wave w, its 8 columns loaded (pair slot i takes columns 4g + i and 4h + i), 4 steps
+// pairing 4g + i with 4h + (i ^ s), s = 0, 1, 3, 2, the second columns moving between slots.
+// Round NG - 1: groups 2w and 2w+1, the 4 columns of each paired in 3 steps ((0,1)(2,3),
+// (0,2)(1,3), (0,3)(1,2)). step(q, a, b) works on step q's pairs.
+template <int U, class F>
+__device__ __forceinline__ void jac_round(double* X, int ng, int w, int r, int slot, int li, F step) {
+  double a[U], b[U];
+  if (r < ng - 1) {
+    int g, h;
+    rr_pair(ng, w, r, g, h);
+    double* pa = X + li + (4 * g + slot) * LDP;
+    jac_load<U>(pa, a);
+    jac_load<U>(X + li + (4 * h + slot) * LDP, b);
+    step(0, a, b);
+    jac_move_b<U, kSlot1>(b);
+    step(1, a, b);
+    jac_move_b<U, kSlot2>(b);
+    step(2, a, b);
+    jac_move_b<U, kSlot1>(b);
+    step(3, a, b);
+    jac_store<U>(pa, a);
+    jac_store<U>(X + li + (4 * h + (slot ^ 2)) * LDP, b);
+  } else {
+    const bool odd = slot & 1;
+    double* X0 = X + li + 4 * (2 * w + (slot >> 1)) * LDP;
+    jac_load<U>(X0 + (odd ? 2 : 0) * LDP, a);
+    jac_load<U>(X0 + (odd ? 3 : 1) * LDP, b);
+    step(0, a, b);
+    jac_swap_ab<U>(a, b, odd);
+    step(1, a, b);
+    jac_move_b<U, kSlot1>(b);
+    step(2, a, b);
+    jac_store<U>(X0 + (odd ? 1 : 0) * LDP, a);
+    jac_store<U>(X0 + (odd ? 2 : 3) * LDP, b);
   }
 }
 
-// A column (into x, vx) from LDS and back; off: the column's and the lane's offset. Every address
-// lies in the 64 x LDP buffers, whose entries past the problem are zero and stay so.
-template <bool WV, int U>
-__device__ __forceinline__ void jac_load(const JacProb& pr, int off, double (&x)[U], double (&vx)[U]) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    x[u] = pr.A[off + 16 * u];
-    if (WV) vx[u] = pr.V[off + 16 * u];
-  }
-}
-
-template <bool WV, int U>
-__device__ __forceinline__ void jac_store(const JacProb& pr, int off, const double (&x)[U], const double (&vx)[U]) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    pr.A[off + 16 * u] = x[u];
-    if (WV) pr.V[off + 16 * u] = vx[u];
-  }
-}
+// LDS of the rotations handed from the waves that make them to those that apply them to V: per buffer
+// and group pair 4 steps of 4 slots. Four waves' worth of A leave as many for V, five three and six two.
+constexpr int kJacCs = 16;
+constexpr int kJacPairs = 6;
+constexpr int kJacWaves = 8;
 
 // Solve a Jacobi problem (A: m x k in LDS, m, k <= 64; V: the k x k accumulated rotations, holding
-// the identity on entry, or null for none) with the workgroup (at least 8 waves). flags: 2 ints of
-// LDS.
+// the identity on entry, or null for none) with the workgroup's first 8 waves. flags: 2 ints of LDS.
 //
-// The k columns are split into NG groups of 4 (NG even, columns past k empty). A sweep is
-//   * NG - 1 group rounds: the round-robin (circle) schedule over the groups gives wave w the
-//     group pair (g, h); the wave loads the 8 columns into registers -- pair slot i takes columns
-//     4g + i and 4h + i -- and runs 4 rounds pairing 4g + i with 4h + (i ^ s), s = 0, 1, 3, 2,
-//     the second columns moving between slots, then stores them back (one workgroup barrier per
-//     group round);
-//   * an intra-group phase: wave w takes groups 2w and 2w+1 and pairs the 4 columns of each in 3
-//     rounds ((0,1)(2,3), (0,2)(1,3), (0,3)(1,2)).
-// Every column pair is visited once per sweep, no two pairs of a round share a column, and no
-// barrier is needed inside a group round.
+// The k columns are split into NG groups of 4 (NG even, columns past k empty); wave w < NG / 2 makes the
+// rounds of jac_round, one workgroup barrier each. Every column pair is visited once per sweep, no
+// two pairs of a step share a column, and no barrier is needed inside a round.
 //
-// Bound by the instruction issue of one wave per SIMD (two at k > 32: 33 to 40 columns make 5 waves, and
-// two of them share a SIMD). Cycles per pair step with V, before this layout and the row classes, and
-// now: 16 columns 1100 -> 620, 32 columns 1140 -> 790, 37 columns 1500 -> 1260, 64 columns 1690 -> 1640.
-// The whole core step at 16, 32 and 37 columns: 66 -> 44, 139 -> 103 and 230 -> 195 us.
-template <bool WV, int U, bool EXACT>
-__device__ int jacobi_waves(const JacProb& pr, int* flags) {
+// SPLIT (at most 6 of the 8 waves on A): the rotations go through LDS (cs) to the other waves, which
+// apply them to V one round later; otherwise each wave rotates V's columns in a second walk over its
+// round.
+//
+// Bound by the chain of a step (dot products, two reciprocal square roots, rotation: about 480 cycles) and
+// by a round's barrier and LDS turn-around, from 33 columns on also by the issue of two waves on a SIMD.
+// Cycles per step with V: one layout for all sizes and lane permutes through LDS; slots and row classes;
+// slot sums by two MFMAs, the shorter rotation and the split: 16 columns 1100, 620, 610; 32 columns 1140,
+// 790, 670 (without the split 770); 37 columns 1500, 1260, 1110 (1190); 64 columns (not split) 1690,
+// 1640, 1540.
+template <bool WV, bool SPLIT, int U, bool EXACT>
+__device__ __forceinline__ int jacobi_waves(const JacProb& pr, int* flags, double2* cs) {
   const int t = threadIdx.x, lane = t & 63;
   const int lw = __builtin_amdgcn_readfirstlane(t >> 6);
   const int slot = (lane >> 2) & 3;
@@ -236,78 +304,62 @@ __device__ int jacobi_waves(const JacProb& pr, int* flags) {
     __syncthreads();
     return 0;
   }
-  const int ng = jac_groups(pr.k);
-  const bool mine = lw < (ng >> 1);
+  const int ng = jac_groups(pr.k), na = ng >> 1;
   const double tol = sqrt((double)max(pr.m, 1)) * kEps;
   const double tol2 = tol * tol;
-  double a[U], b[U], va[U], vb[U];
-  int sweeps = 0;
+  const bool writer = (lane & 51) == 0;  // one lane per slot
+  // the rotations of round r for V, by the waves after A's
+  auto v_round = [&](int r, const double2* buf) __attribute__((always_inline)) {
+    for (int w = lw - na; w < na; w += kJacWaves - na)
+      jac_round<U>(pr.V, ng, w, r, slot, li, [&](int q, double(&a)[U], double(&b)[U]) __attribute__((always_inline)) {
+        const double2 f = buf[w * kJacCs + 4 * q + slot];
+        jac_rotate<U>(a, b, f.x, f.y);
+      });
+  };
+  int sweeps = 0, buf = 0;
   if (t < 2) flags[t] = 0;
   __syncthreads();
   for (int sweep = 0; sweep < 60; ++sweep) {
     sweeps = sweep + 1;
     bool loud = false;  // a rotation above the quiet level
-    for (int gr = 0; gr < ng - 1; ++gr) {
-      if (mine) {
-        int g, h;
-        rr_pair(ng, lw, gr, g, h);
-        const int oa = li + (4 * g + slot) * LDP, ob = li + (4 * h + slot) * LDP;
-        jac_load<WV, U>(pr, oa, a, va);
-        jac_load<WV, U>(pr, ob, b, vb);
-        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 0
-        jac_move_b<WV, U, kSlot1>(b, vb);
-        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 1
-        jac_move_b<WV, U, kSlot2>(b, vb);
-        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 3
-        jac_move_b<WV, U, kSlot1>(b, vb);
-        jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // s = 2
-        jac_store<WV, U>(pr, oa, a, va);
-        jac_store<WV, U>(pr, li + (4 * h + (slot ^ 2)) * LDP, b, vb);
+    for (int r = 0; r < ng; ++r) {
+      double2* now = cs + buf * (kJacPairs * kJacCs);
+      if (lw < na) {
+        double2 f[4];
+        jac_round<U>(pr.A, ng, lw, r, slot, li, [&](int q, double(&a)[U], double(&b)[U]) __attribute__((always_inline)) {
+          f[q] = jac_pair<U, EXACT>(a, b, tol2, loud);
+          if (WV && SPLIT && writer) now[lw * kJacCs + 4 * q + slot] = f[q];
+        });
+        if (WV && !SPLIT)
+          jac_round<U>(pr.V, ng, lw, r, slot, li,
+                       [&](int q, double(&a)[U], double(&b)[U]) __attribute__((always_inline)) { jac_rotate<U>(a, b, f[q].x, f[q].y); });
+        if (r == ng - 1 && __ballot(loud) != 0 && lane == 0) flags[sweep & 1] = 1;
+      } else if (WV && SPLIT && lw < kJacWaves && sweep + r > 0) {
+        v_round(r > 0 ? r - 1 : ng - 1, cs + (buf ^ 1) * (kJacPairs * kJacCs));
       }
       __syncthreads();
+      buf ^= 1;
     }
-    if (mine) {
-      const int c0 = 4 * (2 * lw + (slot >> 1));
-      const bool odd = slot & 1;
-      jac_load<WV, U>(pr, li + (c0 + (odd ? 2 : 0)) * LDP, a, va);
-      jac_load<WV, U>(pr, li + (c0 + (odd ? 3 : 1)) * LDP, b, vb);
-      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,1) (2,3)
-#pragma unroll
-      for (int u = 0; u < U; ++u) {  // even slot: b <- partner's a; odd slot: a <- partner's b
-        const double x = dpp_move<kSlot1>(odd ? a[u] : b[u]);
-        a[u] = odd ? x : a[u];
-        b[u] = odd ? b[u] : x;
-        if (WV) {
-          const double s1 = dpp_move<kSlot1>(odd ? va[u] : vb[u]);
-          va[u] = odd ? s1 : va[u];
-          vb[u] = odd ? vb[u] : s1;
-        }
-      }
-      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,2) (1,3)
-      jac_move_b<WV, U, kSlot1>(b, vb);
-      jac_pair<WV, U, EXACT>(a, b, va, vb, tol2, loud);  // (0,3) (1,2)
-      jac_store<WV, U>(pr, li + (c0 + (odd ? 1 : 0)) * LDP, a, va);
-      jac_store<WV, U>(pr, li + (c0 + (odd ? 2 : 3)) * LDP, b, vb);
-      if (__ballot(loud) != 0 && lane == 0) flags[sweep & 1] = 1;
-    }
-    __syncthreads();
     const bool more = flags[sweep & 1] != 0;
     if (t == 0) flags[(sweep + 1) & 1] = 0;  // set again only past the next sweep's first barrier
     if (!more) break;
   }
+  if (WV && SPLIT) {
+    if (lw >= na && lw < kJacWaves) v_round(ng - 1, cs + (buf ^ 1) * (kJacPairs * kJacCs));
+    __syncthreads();
+  }
   return sweeps;
 }
 
-// Returns the number of sweeps made (the last one made no rotation above the quiet level). EXACT:
-// see slot_sum.
+// Returns the number of sweeps made (the last one made no rotation above the quiet level).
 template <bool WV>
-__device__ __forceinline__ int jacobi(const JacProb& pr, int* flags) {
+__device__ __forceinline__ int jacobi(const JacProb& pr, int* flags, double2* cs) {
   switch ((pr.m + 15) >> 4) {  // uniform; m >= k
     case 0:
-    case 1: return jacobi_waves<WV, 1, false>(pr, flags);
-    case 2: return jacobi_waves<WV, 2, false>(pr, flags);
-    case 3: return jacobi_waves<WV, 3, false>(pr, flags);
-    default: return jacobi_waves<WV, 4, false>(pr, flags);
+    case 1: return jacobi_waves<WV, true, 1, false>(pr, flags, cs);
+    case 2: return jacobi_waves<WV, true, 2, false>(pr, flags, cs);
+    case 3: return jacobi_waves<WV, true, 3, false>(pr, flags, cs);
+    default: return jacobi_waves<WV, false, 4, false>(pr, flags, cs);
   }
 }
 
@@ -687,7 +739,7 @@ __device__ void tri_norms(const double* QR, const double* Ri, int k, double* red
 // sweeps in *sweeps. Mb, Xb, Vq, Cb are distinct 64 x 64 LDS buffers (Mb, Vq are overwritten);
 // tau: kPMax, vbq: 2 kPMax doubles.
 __device__ __forceinline__ int svd_qr(double* Mb, int nJ, int nI, double cut_mult, double* Xb, double* Vq, double* Cb,
-                      double* tau, double* vbq, double* sig, int* ord, double* srt, int* flags, int* sweeps) {
+                      double* tau, double* vbq, double* sig, int* ord, double* srt, int* flags, double2* cs, int* sweeps) {
   const int t = threadIdx.x;
   const bool tall = nJ >= nI;
   const int m = tall ? nJ : nI, k = tall ? nI : nJ;
@@ -704,7 +756,7 @@ __device__ __forceinline__ int svd_qr(double* Mb, int nJ, int nI, double cut_mul
   }
   __syncthreads();
   JacProb pr{Mb, k, k, Vq};
-  *sweeps = jacobi<true>(pr, flags);
+  *sweeps = jacobi<true>(pr, flags, cs);
   norms_sorted(Mb, k, k, sig, ord, srt);
   const double smax = k > 0 ? srt[0] : 0.0;
   const double cut = cut_mult * kEps * smax;
@@ -732,6 +784,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   if (st->done) return;
   __shared__ double B0[kBuf], B1[kBuf], B2[kBuf], B3[kBuf];
   __shared__ double sig[kPMax], srt[kPMax], tau[kPMax], red[16], nrm2[2], vbq[2 * kPMax], dinv[kPMax];
+  __shared__ double2 cs[2 * kJacPairs * kJacCs];
   __shared__ int ord[kPMax], flags[2], posI[kPMax], posJ[kPMax], cnt[2], idxI[kPMax], idxJ[kPMax];
   const int t = threadIdx.x;
   const int nI = st->nIpre, nJ = st->nJpre;
@@ -777,7 +830,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
     set_identity(B1, k0);
     __syncthreads();
     JacProb pr{B0, m0, k0, B1};
-    jacobi_waves<true, 4, true>(pr, flags);
+    jacobi_waves<true, false, 4, true>(pr, flags, cs);
     norms_sorted(B0, m0, k0, sig, ord, srt);
     const double smax = srt[0];
     const double cut = cut_pinv * kEps * smax;
@@ -826,7 +879,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core(Src in) {
   double* Ub = B2;
   double* Vb = B0;
   int sweeps = 0;
-  const int r = svd_qr(M, nJ, nI, cut_pinv, B0, B1, B2, tau, vbq, sig, ord, srt, flags, &sweeps);
+  const int r = svd_qr(M, nJ, nI, cut_pinv, B0, B1, B2, tau, vbq, sig, ord, srt, flags, cs, &sweeps);
   // now Ub = U^ (nJ x r), Vb = V~ (nI x r), singular values srt[0..r)
   for (int e = t; e < r * pm; e += blockDim.x) {
     const int i = e % pm, rr = e / pm;
@@ -1031,7 +1084,7 @@ __global__ __launch_bounds__(kEtaThreads) void k_eta(Src in) {
     lds_gemm(Qs, Us, E, ns, r, kc, !tall);
     __syncthreads();
     const JacProb pr{E, tall ? ns : r, tall ? r : ns, nullptr};
-    jacobi<false>(pr, flags);
+    jacobi<false>(pr, flags, nullptr);
     if (t < 64) {  // smallest column norm
       double v = INFINITY;
       if (t < pr.k) {
@@ -1099,6 +1152,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
   if (st->done) return;
   __shared__ double B0[kBuf], B1[kBuf], B2[kBuf], B3[kBuf];
   __shared__ double sig[kPMax], srt[kPMax], tau[kPMax], vbq[2 * kPMax];
+  __shared__ double2 cs[2 * kJacPairs * kJacCs];
   __shared__ int ord[kPMax], flags[2];
   const int t = threadIdx.x;
   // the width of the start: the right-hand side's rank, or the guess's columns
@@ -1118,7 +1172,7 @@ __global__ __launch_bounds__(kCoreThreads) void k_core_warm(CoreArgs a) {
   }
   __syncthreads();
   int sweeps = 0;
-  const int r = svd_qr(B3, rF, rF, (double)rF, B0, B1, B2, tau, vbq, sig, ord, srt, flags, &sweeps);
+  const int r = svd_qr(B3, rF, rF, (double)rF, B0, B1, B2, tau, vbq, sig, ord, srt, flags, cs, &sweeps);
   // a zero guess leaves the start from the right-hand side in place
   if (a.guess && r == 0) {
     if (t == 0) st->guess_ok = 0;
