@@ -353,7 +353,8 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   io.Q[1] = c->Q[1];
   io.ldq = n;
   io.columns = keep_rounding(c);
-  TRY(tsqr_run(c->tsqr, io, s));
+  const bool fold = tsqr_can_fold(c->tsqr);
+  TRY(fold ? tsqr_run_rows(c->tsqr, io, true, s) : tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
   ca.Q0 = c->Q[0];
@@ -381,7 +382,7 @@ int enqueue_pass_update(lrp_ctx* c, int k) {
   pa.ldo = n;
   pa.n = n;
   pa.nb = nb_new;
-  TRY(prod_launch(pa, s));
+  TRY(fold ? tsqr_fold(c->tsqr, io, pa, s) : prod_launch(pa, s));
   RhoArgs ra{};
   ra.st = c->st;
   ra.Unew[0] = c->Uit[nb_new];
@@ -535,7 +536,8 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   io.Q[1] = c->Q[1];
   io.ldq = n;
   io.columns = keep_rounding(c);
-  TRY(tsqr_run(c->tsqr, io, s));
+  const bool fold = tsqr_can_fold(c->tsqr);
+  TRY(fold ? tsqr_run_rows(c->tsqr, io, false, s) : tsqr_run(c->tsqr, io, s));
   CoreArgs ca{};
   ca.st = c->st;
   ca.R0 = tsqr_R(c->tsqr, 0);
@@ -560,7 +562,7 @@ int enqueue_start(lrp_ctx* c, int rF, const double* U_F, int64_t ldu, const doub
   pa.ldo = n;
   pa.n = n;
   pa.nb = 0;
-  TRY(prod_launch(pa, s));
+  TRY(fold ? tsqr_fold(c->tsqr, io, pa, s) : prod_launch(pa, s));
   if (c->guess_r0 > 0) TRY(enqueue_guess(c));
   const double* U[2] = {c->Uit[0], c->Vit[0]};
   return enqueue_selection(c, U);

@@ -184,11 +184,47 @@ struct TsqrIO {
   int columns;         // 1: the column kernels of tsqr.hip, else the panel kernels (tsqr_panel.hip)
 };
 
+// What a launch of Q's formation covers.
+struct ApplySel {
+  int pick;    // 1: only the blocks that hold the rows Ipre (side 0) and Jpre (side 1)
+  int out_nb;  // -1: Y has the block's p columns; else the parent pieces and Y have st->r[out_nb]
+};
+struct ApplyOut {
+  const double* T[2];  // parent pieces, ld ldt; null = identity
+  int64_t ldt;
+  double* Y[2];
+  int64_t ldy;
+  ApplySel sel;
+};
+__device__ __forceinline__ int apply_block(const DevState* st, const ApplySel& sel, int side, int block_rows) {
+  const int b = blockIdx.x;
+  if (!sel.pick) return b;
+  if (b >= (side == 0 ? st->nIpre : st->nJpre)) return -1;
+  return __builtin_amdgcn_readfirstlane((side == 0 ? st->Ipre : st->Jpre)[b]) / block_rows;
+}
+__device__ __forceinline__ int apply_cols(const DevState* st, const ApplySel& sel, int p) {
+  return sel.out_nb < 0 ? p : __builtin_amdgcn_readfirstlane(st->r[sel.out_nb]);
+}
+
 int tsqr_plan(TsqrPlan* p, int64_t n, int pmax);
 int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s);
+// The products U = Q U^ folded into Q's formation. Q = diag(Q_b) Y_1 with the leaves' factors Q_b and
+// Y_1 of level 1, so U = diag(Q_b) (Y_1 U^): the product is taken on Y_1's rows (p_max per 256 of Q's) and
+// the leaves form U where they would form Q. tsqr_run_rows: the factorization and the levels above
+// the leaves, and with `rows` the leaf blocks of Q that hold the rows Ipre (Q) and Jpre (Z), which is all
+// of Q that the core and the indicator read, bit for bit as tsqr_run forms them. tsqr_fold: pa's product
+// (pa.Q is not read), through level 1's V, which is free by then. What it saves, three quarters of the
+// product and of its traffic, has to pay for the launch of the picked blocks: ms per solve without and
+// with it at n = 65535 1.56, 1.55 (mixed, cap 64); 131071 2.19, 2.14; 262143 3.15, 3.00; 2^20 - 1 9.44,
+// 8.39, and in FP64 at caps 32 and 64 11.4, 10.1 and 21.9, 20.2.
+constexpr int64_t kTsqrFoldRows = int64_t(1) << 16;
+bool tsqr_can_fold(const TsqrPlan& p);
+int tsqr_run_rows(const TsqrPlan& p, const TsqrIO& io, bool rows, hipStream_t s);
+struct ProdArgs;
+int tsqr_fold(const TsqrPlan& p, const TsqrIO& io, ProdArgs pa, hipStream_t s);
 // The panel kernels' factorization of level L's blocks, and their part of Q (tsqr_panel.hip).
 int tsqr_panel_factor(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s);
-int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s);
+int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOut& o, hipStream_t s);
 // Final R of side `side` (pmax x pmax, ld pmax, upper triangular).
 inline const double* tsqr_R(const TsqrPlan& p, int side) { return p.lev[p.nlevels - 1].Rout[side]; }
 

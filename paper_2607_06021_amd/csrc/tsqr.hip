@@ -48,6 +48,7 @@ struct ApplyArgs {
   int64_t ldt;
   double* Y[2];
   int64_t ldy;
+  ApplySel sel;
 };
 
 // An empty asm statement that takes a loaded value as input and output: the load must then
@@ -354,7 +355,10 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
   const int side = blockIdx.y;
   if (a.st && a.st->done) return;
   const int p = side_cols(a.st, a.ncols, side);
-  const int64_t row0 = (int64_t)blockIdx.x * a.block_rows;
+  const int block = apply_block(a.st, a.sel, side, a.block_rows);
+  const int oc = apply_cols(a.st, a.sel, p);  // columns of T_par and of Y
+  if (block < 0 || oc <= 0) return;
+  const int64_t row0 = (int64_t)block * a.block_rows;
   const int nr = (int)min((int64_t)a.block_rows, a.rows - row0);
   if (p <= 0 || nr <= 0) return;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -363,13 +367,14 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
   constexpr int kWaves = kWyThreads / 64;
   __shared__ double Vs[kHalf * kWyLd];  // V(r, c) of one half at Vs[r kWyLd + c], zero past p / nr
   __shared__ double S[kPMax * kWyLd];   // v_i . v_k (upper tiles; the rest zero)
-  __shared__ double XZ[kPMax * kWyLd];  // X, then Z in place; zero outside p x p
+  __shared__ double XZ[kPMax * kWyLd];  // X, then Z in place; zero outside p x oc
   __shared__ double tsh[kPMax];
   const double* V = a.V[side] + row0;  // V(r, c) = V[r + c ldv], r < nr, c < p
   const int64_t ldv = a.ldv;
   const double* T = a.T[side];
-  const int64_t toff = (int64_t)blockIdx.x * a.pmax;
+  const int64_t toff = (int64_t)block * a.pmax;
   const int pt = (p + 15) >> 4;  // 16-column tiles in use
+  const int ot = (oc + 15) >> 4;  // of Y's columns
   const int pk = (p + 3) >> 2;   // 4-row steps over p
   const int ntiles = pt * (pt + 1) / 2;
 
@@ -406,14 +411,14 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
       const int e = t + kWyThreads * m, r = e % kHalf, c = e / kHalf;
       raw[h][m] = V[min(h * kHalf + r, nr - 1) + (int64_t)min(c, p - 1) * ldv];
     }
-  // and the parent piece T_par (p x p), kept in registers until V's staging buffer is free
+  // and the parent piece T_par (p x oc), kept in registers until V's staging buffer is free
   constexpr int kTPer = kPMax * kPMax / kWyThreads;  // 8
   double tpre[kTPer];
   if (T) {
 #pragma unroll
     for (int m = 0; m < kTPer; ++m) {
       const int e = t + kWyThreads * m, r = e % kPMax, c = e / kPMax;
-      tpre[m] = T[toff + min(r, p - 1) + (int64_t)min(c, p - 1) * a.ldt];
+      tpre[m] = T[toff + min(r, p - 1) + (int64_t)min(c, oc - 1) * a.ldt];
     }
   }
 
@@ -445,20 +450,20 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const int q = wave + kWaves * m;
-        if (q >= pt * pt) continue;
-        const int I = q / pt, J = q % pt;
+        if (q >= pt * ot) continue;
+        const int I = q / ot, J = q % ot;
         for (int k0 = 4 * I; k0 < pk; k0 += 4) {
           double tv[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
-            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, p - 1) * a.ldt];
+            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, oc - 1) * a.ldt];
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
             keep_loaded(tv[u]);
-            const double b = (r < p && 16 * J + lr < p) ? tv[u] : 0.0;
+            const double b = (r < p && 16 * J + lr < oc) ? tv[u] : 0.0;
             xacc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Vs[r * kWyLd + 16 * I + lr], b, xacc[m], 0, 0, 0);
           }
         }
@@ -480,13 +485,13 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     __syncthreads();
     }
   }
-  // V's staging buffer now holds T_par (zero outside p x p) for the final product
+  // V's staging buffer now holds T_par (zero outside p x oc) for the final product
   if (T) {
 #pragma unroll
     for (int m = 0; m < kTPer; ++m) {
       const int e = t + kWyThreads * m, r = e % kPMax, c = e / kPMax;
       keep_loaded(tpre[m]);
-      Vs[r * kWyLd + c] = (r < p && c < p) ? tpre[m] : 0.0;
+      Vs[r * kWyLd + c] = (r < p && c < oc) ? tpre[m] : 0.0;
     }
   }
 #pragma unroll
@@ -499,8 +504,8 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const int q = wave + kWaves * m;
-      if (q >= pt * pt) continue;
-      const int I = q / pt, J = q % pt;
+      if (q >= pt * ot) continue;
+      const int I = q / ot, J = q % ot;
 #pragma unroll
       for (int v = 0; v < 4; ++v) XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr] = xacc[m][v];
     }
@@ -534,8 +539,8 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     }
     __syncthreads();
     if (b == 0) break;
-    for (int q = wave; q < b * pt; q += kWaves) {  // tile (I, J): rows 16 I, columns 16 J
-      const int I = q / pt, J = q % pt;
+    for (int q = wave; q < b * ot; q += kWaves) {  // tile (I, J): rows 16 I, columns 16 J
+      const int I = q / ot, J = q % ot;
       wy4 acc;
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[v] = XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr];
@@ -557,7 +562,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     const int row = 16 * R + lr;
     if (16 * R >= nr) continue;  // uniform
     wy4 acc[4];
-    if (T) {  // Y0 = [T_par; 0], T_par staged in LDS (zero outside p x p)
+    if (T) {  // Y0 = [T_par; 0], T_par staged in LDS (zero outside p x oc)
 #pragma unroll
       for (int J = 0; J < 4; ++J)
 #pragma unroll
@@ -574,7 +579,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
       const double* Zk = XZ + (4 * ks + lk) * kWyLd + lr;
 #pragma unroll
       for (int J = 0; J < 4; ++J)
-        if (J < pt) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], h == 0 ? vb0[ks] : vb1[ks], acc[J], 0, 0, 0);
+        if (J < ot) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], h == 0 ? vb0[ks] : vb1[ks], acc[J], 0, 0, 0);
     }
     if (row < nr) {
 #pragma unroll
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int col = 16 * J + lk + 4 * v;
-          if (col < p) Y[row + (int64_t)col * a.ldy] = acc[J][v];
+          if (col < oc) Y[row + (int64_t)col * a.ldy] = acc[J][v];
         }
     }
   }
@@ -600,7 +605,10 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
   const int side = blockIdx.y;
   if (a.st && a.st->done) return;
   const int p = side_cols(a.st, a.ncols, side);
-  const int64_t row0 = (int64_t)blockIdx.x * a.block_rows;
+  const int block = apply_block(a.st, a.sel, side, a.block_rows);
+  const int oc = apply_cols(a.st, a.sel, p);  // columns of T_par and of Y
+  if (block < 0 || oc <= 0) return;
+  const int64_t row0 = (int64_t)block * a.block_rows;
   const int nr = (int)min((int64_t)a.block_rows, a.rows - row0);
   if (p <= 0 || nr <= 0) return;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -608,13 +616,14 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
   constexpr int kQuarter = kPMax;         // rows of V staged at a time (= the rows of S)
   constexpr int kWaves = kWyThreads / 64;
   __shared__ double QS[kQuarter * kWyLd];  // V(r, c) of one quarter, zero past p / nr; then S
-  __shared__ double XZ[kPMax * kWyLd];     // X, then Z in place; zero outside p x p
+  __shared__ double XZ[kPMax * kWyLd];     // X, then Z in place; zero outside p x oc
   __shared__ double tsh[kPMax];
   const double* V = a.V[side] + row0;  // V(r, c) = V[r + c ldv], r < nr, c < p
   const int64_t ldv = a.ldv;
   const double* T = a.T[side];
-  const int64_t toff = (int64_t)blockIdx.x * a.pmax;
+  const int64_t toff = (int64_t)block * a.pmax;
   const int pt = (p + 15) >> 4;
+  const int ot = (oc + 15) >> 4;  // of Y's columns
   const int pk = (p + 3) >> 2;
   const int ntiles = pt * (pt + 1) / 2;
 
@@ -664,20 +673,20 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const int q = wave + kWaves * m;
-        if (q >= pt * pt) continue;
-        const int I = q / pt, J = q % pt;
+        if (q >= pt * ot) continue;
+        const int I = q / ot, J = q % ot;
         for (int k0 = 4 * I; k0 < pk; k0 += 4) {
           double tv[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
-            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, p - 1) * a.ldt];
+            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, oc - 1) * a.ldt];
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
             keep_loaded(tv[u]);
-            const double b = (r < p && 16 * J + lr < p) ? tv[u] : 0.0;
+            const double b = (r < p && 16 * J + lr < oc) ? tv[u] : 0.0;
             xacc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(QS[r * kWyLd + 16 * I + lr], b, xacc[m], 0, 0, 0);
           }
         }
@@ -699,8 +708,8 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const int q = wave + kWaves * m;
-      if (q >= pt * pt) continue;
-      const int I = q / pt, J = q % pt;
+      if (q >= pt * ot) continue;
+      const int I = q / ot, J = q % ot;
 #pragma unroll
       for (int v = 0; v < 4; ++v) XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr] = xacc[m][v];
     }
@@ -729,8 +738,8 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
     }
     __syncthreads();
     if (b == 0) break;
-    for (int q = wave; q < b * pt; q += kWaves) {
-      const int I = q / pt, J = q % pt;
+    for (int q = wave; q < b * ot; q += kWaves) {
+      const int I = q / ot, J = q % ot;
       wy4 acc;
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[v] = XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr];
@@ -765,7 +774,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int c = 16 * J + lk + 4 * v;
-          tp[J][v] = T[toff + min(row, p - 1) + (int64_t)min(c, p - 1) * a.ldt];
+          tp[J][v] = T[toff + min(row, p - 1) + (int64_t)min(c, oc - 1) * a.ldt];
         }
 #pragma unroll
       for (int J = 0; J < 4; ++J)
@@ -773,7 +782,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
         for (int v = 0; v < 4; ++v) {
           const int c = 16 * J + lk + 4 * v;
           keep_loaded(tp[J][v]);
-          acc[J][v] = (row < p && c < p) ? tp[J][v] : 0.0;
+          acc[J][v] = (row < p && c < oc) ? tp[J][v] : 0.0;
         }
     } else {
 #pragma unroll
@@ -792,7 +801,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
       const double* Zk = XZ + (4 * ks + lk) * kWyLd + lr;
 #pragma unroll
       for (int J = 0; J < 4; ++J)
-        if (J < pt) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], vb[ks], acc[J], 0, 0, 0);
+        if (J < ot) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], vb[ks], acc[J], 0, 0, 0);
     }
     if (row < nr) {
 #pragma unroll
@@ -800,7 +809,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int col = 16 * J + lk + 4 * v;
-          if (col < p) Y[row + (int64_t)col * a.ldy] = acc[J][v];
+          if (col < oc) Y[row + (int64_t)col * a.ldy] = acc[J][v];
         }
     }
   }
@@ -853,21 +862,15 @@ int tsqr_plan(TsqrPlan* p, int64_t n, int pmax) {
   });
 }
 
-int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
-  if (!io.columns) {  // the panel kernels
-    for (int L = 0; L < p.nlevels; ++L) {
+// Bottom-up factorization of all levels.
+static int factor_levels(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
+  const int ns = io.nsides;
+  for (int L = 0; L < p.nlevels; ++L) {
+    if (!io.columns) {
       const int rc = tsqr_panel_factor(p, L, io, s);
       if (rc != LRP_OK) return rc;
+      continue;
     }
-    for (int L = p.nlevels - 1; L >= 0; --L) {
-      const int rc = tsqr_panel_apply(p, L, io, s);
-      if (rc != LRP_OK) return rc;
-    }
-    return LRP_OK;
-  }
-  const int ns = io.nsides;
-  // bottom-up factorization
-  for (int L = 0; L < p.nlevels; ++L) {
     const TsqrLevel& lv = p.lev[L];
     FactorArgs f{};
     f.st = io.st;
@@ -900,31 +903,86 @@ int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
     else
       LRP_LAUNCH_G(K_TSQR_FACTOR, k_tsqr_factor<FactorArgs>, k_tsqr_factor<GroupRef>, dim3(lv.nblocks, ns), dim3(kTsqrThreads), 0, s, f);
   }
-  // top-down formation of Q
-  for (int L = p.nlevels - 1; L >= 0; --L) {
-    const TsqrLevel& lv = p.lev[L];
-    ApplyArgs a{};
-    a.st = io.st;
-    a.ncols[0] = io.ncols[0];
-    a.ncols[1] = io.ncols[1];
-    a.ldv = lv.rows;
-    a.rows = lv.rows;
-    a.block_rows = lv.block_rows;
-    a.pmax = p.pmax;
-    for (int q = 0; q < 2; ++q) {
-      a.V[q] = lv.V[q];
-      a.tau[q] = lv.tau[q];
-      a.T[q] = (L == p.nlevels - 1) ? nullptr : p.lev[L + 1].Y[q];
-      a.Y[q] = (L == 0 && io.Q[q]) ? io.Q[q] : lv.Y[q];
-    }
-    a.ldt = (L == p.nlevels - 1) ? 0 : p.lev[L + 1].rows;
-    a.ldy = (L == 0 && io.Q[0]) ? io.ldq : lv.rows;
-    if ((int64_t)lv.nblocks * ns > kCUs)
-      LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_lean<ApplyArgs>, k_tsqr_apply_lean<GroupRef>, dim3(lv.nblocks, ns), dim3(kWyThreads), 0, s, a);
-    else
-      LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_wy<ApplyArgs>, k_tsqr_apply_wy<GroupRef>, dim3(lv.nblocks, ns), dim3(kWyThreads), 0, s, a);
-  }
   return launch_status();
+}
+
+// Level L's part of Q from its parent's, o.T of nT rows (null: identity), into o.Y.
+static int apply_level(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOut& o, hipStream_t s) {
+  if (!io.columns) return tsqr_panel_apply(p, L, io, o, s);
+  const TsqrLevel& lv = p.lev[L];
+  ApplyArgs a{};
+  a.st = io.st;
+  a.ncols[0] = io.ncols[0];
+  a.ncols[1] = io.ncols[1];
+  a.ldv = lv.rows;
+  a.rows = lv.rows;
+  a.block_rows = lv.block_rows;
+  a.pmax = p.pmax;
+  a.ldt = o.ldt;
+  a.ldy = o.ldy;
+  a.sel = o.sel;
+  for (int q = 0; q < 2; ++q) {
+    a.V[q] = lv.V[q];
+    a.tau[q] = lv.tau[q];
+    a.T[q] = o.T[q];
+    a.Y[q] = o.Y[q];
+  }
+  const int nblocks = o.sel.pick ? p.pmax : lv.nblocks;
+  if ((int64_t)nblocks * io.nsides > kCUs)
+    LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_lean<ApplyArgs>, k_tsqr_apply_lean<GroupRef>, dim3(nblocks, io.nsides), dim3(kWyThreads), 0, s, a);
+  else
+    LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_wy<ApplyArgs>, k_tsqr_apply_wy<GroupRef>, dim3(nblocks, io.nsides), dim3(kWyThreads), 0, s, a);
+  return launch_status();
+}
+
+// Where level L's part of Q comes from and goes to in a full formation of Q.
+static ApplyOut level_out(const TsqrPlan& p, int L, const TsqrIO& io) {
+  const bool root = L == p.nlevels - 1, own = L == 0 && io.Q[0];
+  ApplyOut o{};
+  o.sel.out_nb = -1;
+  o.ldt = root ? 0 : p.lev[L + 1].rows;
+  o.ldy = own ? io.ldq : p.lev[L].rows;
+  for (int q = 0; q < 2; ++q) {
+    o.T[q] = root ? nullptr : p.lev[L + 1].Y[q];
+    o.Y[q] = own ? io.Q[q] : p.lev[L].Y[q];
+  }
+  return o;
+}
+
+int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
+  int rc = factor_levels(p, io, s);
+  for (int L = p.nlevels - 1; L >= 0 && rc == LRP_OK; --L) rc = apply_level(p, L, io, level_out(p, L, io), s);
+  return rc;
+}
+
+bool tsqr_can_fold(const TsqrPlan& p) { return p.nlevels > 1 && p.n >= kTsqrFoldRows; }
+
+int tsqr_run_rows(const TsqrPlan& p, const TsqrIO& io, bool rows, hipStream_t s) {
+  int rc = factor_levels(p, io, s);
+  for (int L = p.nlevels - 1; L > 0 && rc == LRP_OK; --L) rc = apply_level(p, L, io, level_out(p, L, io), s);
+  if (rows && rc == LRP_OK) {
+    ApplyOut o = level_out(p, 0, io);
+    o.sel.pick = 1;
+    rc = apply_level(p, 0, io, o, s);
+  }
+  return rc;
+}
+
+int tsqr_fold(const TsqrPlan& p, const TsqrIO& io, ProdArgs pa, hipStream_t s) {
+  const TsqrLevel& up = p.lev[1];
+  ApplyOut o{};
+  o.sel.out_nb = pa.nb;
+  o.ldt = up.rows;
+  o.ldy = pa.ldo;
+  for (int q = 0; q < 2; ++q) {
+    o.T[q] = up.V[q];
+    o.Y[q] = pa.out[q];
+    pa.Q[q] = up.Y[q];
+    pa.out[q] = up.V[q];
+  }
+  pa.ldq = pa.ldo = pa.n = up.rows;
+  const int rc = prod_launch(pa, s);
+  return rc == LRP_OK ? apply_level(p, 0, io, o, s) : rc;
 }
 
 // ----------------------------------------------------------------------------------------

@@ -42,6 +42,7 @@ struct PanelApplyArgs {
   int64_t ldt;
   double* Y[2];
   int64_t ldy;
+  ApplySel sel;
   uint8_t cls[4];
 };
 
@@ -522,7 +523,10 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
   const int side = blockIdx.y;
   if (a.st && a.st->done) return;
   const int p = __builtin_amdgcn_readfirstlane(side_cols(a.st, a.ncols, side));
-  const int64_t row0 = (int64_t)blockIdx.x * a.block_rows;
+  const int block = apply_block(a.st, a.sel, side, a.block_rows);
+  const int oc = apply_cols(a.st, a.sel, p);  // columns of T_par and of Y
+  if (block < 0 || oc <= 0) return;
+  const int64_t row0 = (int64_t)block * a.block_rows;
   const int nr = (int)min((int64_t)a.block_rows, a.rows - row0);
   if (p <= 0 || nr <= 0) return;
   const int t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
@@ -557,14 +561,14 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int e = 0; e < 16; ++e) tp[e] = 4 * e + g == col ? 1.0 : 0.0;
     if (T) {
-      const double* Tc = T + (int64_t)blockIdx.x * a.pmax + (int64_t)min(col, p - 1) * a.ldt;
+      const double* Tc = T + (int64_t)block * a.pmax + (int64_t)min(col, oc - 1) * a.ldt;
 #pragma unroll
       for (int e = 0; e < 16; ++e) tp[e] = Tc[min(4 * e + g, p - 1)];
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       keep_loaded(tp[e]);
-      y[e >> 2][e & 3] = (4 * e + g < p && col < p) ? tp[e] : 0.0;
+      y[e >> 2][e & 3] = (4 * e + g < p && col < oc) ? tp[e] : 0.0;
     }
   }
   for (int P = pt - 1; P >= 0; --P) {
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     vs = Vs[P & 1];
     if (P > 0) fetch(P - 1);
     __syncthreads();
-    if (kPanel * w < p) {  // uniform
+    if (kPanel * w < oc) {  // uniform
       // V_P^T Y; before the first panel Y is zero past the first 64 rows
       wy4 W = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -616,10 +620,10 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
   }
   // Out through LDS, so that a store covers 64 consecutive rows of a column (in the tile layout it
   // would touch 16 cache lines). The buffer is free: its panel was consumed before the last barrier.
-  if (kPanel * w < p) {
+  if (kPanel * w < oc) {
     double* st = Vs[1] + w * (kTsqrRows / 4) * kVLd;
     double* Yr = a.Y[side] + row0 + (int64_t)(kPanel * w) * a.ldy + lane;
-    const int cols = min(kPanel, p - kPanel * w);
+    const int cols = min(kPanel, oc - kPanel * w);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
 #pragma unroll
@@ -672,25 +676,25 @@ int tsqr_panel_factor(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s)
   return launch_status();
 }
 
-int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s) {
+int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOut& o, hipStream_t s) {
   const TsqrLevel& lv = p.lev[L];
-  const bool root = L == p.nlevels - 1, own = L == 0 && io.Q[0];
   PanelApplyArgs a{};
   a.st = io.st;
   a.rows = lv.rows;
   a.block_rows = lv.block_rows;
   a.pmax = p.pmax;
-  a.ldt = root ? 0 : p.lev[L + 1].rows;
-  a.ldy = own ? io.ldq : lv.rows;
+  a.ldt = o.ldt;
+  a.ldy = o.ldy;
+  a.sel = o.sel;
   tile_classes(p, L, a.cls);
   for (int q = 0; q < 2; ++q) {
     a.ncols[q] = io.ncols[q];
     a.V[q] = lv.V[q];
-    a.T[q] = root ? nullptr : p.lev[L + 1].Y[q];
-    a.Y[q] = own ? io.Q[q] : lv.Y[q];
+    a.T[q] = o.T[q];
+    a.Y[q] = o.Y[q];
   }
-  LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_panel_apply<PanelApplyArgs>, k_tsqr_panel_apply<GroupRef>, dim3(lv.nblocks, io.nsides),
-               dim3(kWyThreads), 0, s, a);
+  LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_panel_apply<PanelApplyArgs>, k_tsqr_panel_apply<GroupRef>,
+               dim3(o.sel.pick ? p.pmax : lv.nblocks, io.nsides), dim3(kWyThreads), 0, s, a);
   return launch_status();
 }
 

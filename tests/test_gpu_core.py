@@ -42,3 +42,13 @@ def test_rho_row_blocks(n):
     g = gpu_solve(n, U, s, V, 32, 1e-10, 20)
     assert any(np.isfinite(t["rho"]) for t in g["trace"])
     compare_fp64(g, o, f"rho n={n}")
+
+
+@pytest.mark.parametrize("n", [65535, 65536])
+def test_product_folded_into_q(n):
+    """Both sides of the size from which the factors' products are taken above the leaves of the QR
+    tree (the larger sizes and the column kernels: the n = 2^20 - 1 tests against stored values)."""
+    U, s, V = workloads.make(workloads.CONFIGS["n4095_r10_fp64"], 1, n=n)
+    print(f"fold n={n}", flush=True)
+    o = cd.solve(n, U, s, V, 32, 1e-10, 20)
+    compare_fp64(gpu_solve(n, U, s, V, 32, 1e-10, 20), o, f"fold n={n}")
