@@ -184,7 +184,9 @@ __host__ __device__ constexpr int seq_len(int P) { return P + P / 16 + 1; }
 // share a CU where whole complex values and 160 VGPRs left one (8 waves); their memory phases cover
 // each other's barriers. FP64, both passes: 56 -> 43 us at n = 65535, 64 columns (134 MB in four
 // passes over memory); 89 -> 67 at n = 262143, 30 columns; 394 -> 372 at n = 2^20 - 1, 30 columns.
-template <typename T, int E, int P, int R, int LS>
+// WHOLE: complex values at once, half the barriers, for the one-pass transforms, whose few small
+// workgroups wait on nothing else.
+template <typename T, int E, int P, int R, int LS, bool WHOLE>
 __device__ __forceinline__ void stage(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   constexpr int TP = P / E, NB = E / R;
   constexpr bool kLast = (LS * R == P);
@@ -215,49 +217,72 @@ __device__ __forceinline__ void stage(cx<T> (&x)[E], T* lds, int tt, const cx<T>
     static_assert(TP % LS == 0, "stage order");
     constexpr bool kLin = NB == 1 || TP * R % 16 == 0, kLinIn = TP % 16 == 0;
     const int k = tt & (LS - 1);
-    T* out = lds + pad((tt - k) * R + k);
-    T* in = lds + pad(tt);
+    const int out = pad((tt - k) * R + k), in = pad(tt);
 #pragma unroll
-    for (int part = 0; part < 2; ++part) {
+    for (int part = 0; part < (WHOLE ? 1 : 2); ++part) {
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-          const T v = part == 0 ? y[i + NB * q].x : y[i + NB * q].y;
-          if (kLin)
-            out[pad(TP * R * i) + pad(q * LS)] = v;
+          const cx<T> z = y[i + NB * q];
+          const int at = kLin ? pad(TP * R * i) + pad(q * LS) + out : pad((tt - k + TP * i) * R + k + q * LS);
+          if (WHOLE)
+            reinterpret_cast<cx<T>*>(lds)[at] = z;
           else
-            lds[pad((tt - k + TP * i) * R + k + q * LS)] = v;
+            lds[at] = part == 0 ? z.x : z.y;
         }
       __syncthreads();
 #pragma unroll
-      for (int e = 0; e < E; ++e) (part == 0 ? x[e].x : x[e].y) = kLinIn ? in[pad(TP * e)] : lds[pad(tt + TP * e)];
+      for (int e = 0; e < E; ++e) {
+        const int at = kLinIn ? pad(TP * e) + in : pad(tt + TP * e);
+        if (WHOLE)
+          x[e] = reinterpret_cast<const cx<T>*>(lds)[at];
+        else
+          (part == 0 ? x[e].x : x[e].y) = lds[at];
+      }
     }
   }
 }
 
-template <typename T, int E, int P, int LS>
+template <typename T, int E, int P, int LS, bool WHOLE>
 __device__ __forceinline__ void stages16(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   if constexpr (LS < P) {
-    stage<T, E, P, 16, LS>(x, lds, tt, tw);
-    stages16<T, E, P, LS * 16>(x, lds, tt, tw);
+    stage<T, E, P, 16, LS, WHOLE>(x, lds, tt, tw);
+    stages16<T, E, P, LS * 16, WHOLE>(x, lds, tt, tw);
   }
 }
 
 // Forward DFT of one sequence of length 2^LOGP held as x[e] = element tt + (P/E) e; tw[j] = W_P^j.
 // Every thread of the block must call it (it contains barriers).
-template <typename T, int LOGP, int E>
+template <typename T, int LOGP, int E, bool WHOLE = false>
 __device__ __forceinline__ void fft_seq(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   constexpr int P = 1 << LOGP;
   constexpr int R0 = 1 << (LOGP % 4 == 0 ? 4 : LOGP % 4);
-  stage<T, E, P, R0, 1>(x, lds, tt, tw);
-  stages16<T, E, P, R0>(x, lds, tt, tw);
+  stage<T, E, P, R0, 1, WHOLE>(x, lds, tt, tw);
+  stages16<T, E, P, R0, WHOLE>(x, lds, tt, tw);
 }
 
 // ---------------------------------------------------------------- data access helpers
+// The workgroup's column set: both sets' fields are read at fixed offsets and selected (an indexed read
+// would wait for the index first, a third of a microsecond in a one-pass transform).
+__device__ __forceinline__ DstSide my_side(const DstArgs& a) {
+  const DstSide &u = a.side[0], &v = a.side[1];
+  const bool y = blockIdx.y != 0;
+  DstSide d;
+  d.X = y ? v.X : u.X;
+  d.X1 = y ? v.X1 : u.X1;
+  d.ldx = y ? v.ldx : u.ldx;
+  d.Y = y ? v.Y : u.Y;
+  d.Yf = y ? v.Yf : u.Yf;
+  d.ldy = y ? v.ldy : u.ldy;
+  d.scale = y ? v.scale : u.scale;
+  d.outscale = y ? v.outscale : u.outscale;
+  return d;
+}
+
 __device__ inline bool dst_resolve(const DstArgs& a, const double*& X, int& ncols) {
-  const DstSide& d = a.side[blockIdx.y];
+  const DstSide d = my_side(a);
   X = d.X;
   ncols = a.ncols;
   if (a.st) {
@@ -272,7 +297,7 @@ __device__ inline bool dst_resolve(const DstArgs& a, const double*& X, int& ncol
 }
 
 __device__ inline void col_scales(const DstArgs& a, int ca, int cb, int ncols, double& sa, double& sb) {
-  const DstSide& d = a.side[blockIdx.y];
+  const DstSide d = my_side(a);
   sa = d.outscale;
   sb = d.outscale;
   if (d.scale) {
@@ -326,7 +351,7 @@ __device__ __forceinline__ void put_pair(const DstArgs& a, int ca, int cb, int n
                                          double sa, double sb) {
   const double va = ca < ncols ? -(double)Z.y * sa : 0.0;
   const double vb = cb < ncols ? (double)Z.x * sb : 0.0;
-  const DstSide& d = a.side[blockIdx.y];
+  const DstSide d = my_side(a);
   if (d.Yf) {  // FP32 destination (spectral factors of the mixed-precision path)
     d.Yf[(k - 1) + (int64_t)ca * d.ldy] = (float)va;
     if (cb < a.ncols_out) d.Yf[(k - 1) + (int64_t)cb * d.ldy] = (float)vb;
@@ -377,19 +402,19 @@ template <typename T, int LOGL>
 __global__ __launch_bounds__(512) void k_dst_single(DstArgs a) {
   constexpr int L = 1 << LOGL, E = L < 16 ? L : 16, TP = L / E;
   constexpr int SEQS = single_seqs(LOGL), SEQ = seq_len(L);
-  __shared__ T lds[SEQS * SEQ];
+  __shared__ __align__(16) T lds[2 * SEQS * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
   const int tt = threadIdx.x % TP, sl = threadIdx.x / TP;
   const int ca = 2 * (blockIdx.x * SEQS + sl), cb = ca + 1;
   const int64_t M = L / 2;
-  const double* xa = ca < ncols ? X + (int64_t)ca * a.side[blockIdx.y].ldx : nullptr;
-  const double* xb = cb < ncols ? X + (int64_t)cb * a.side[blockIdx.y].ldx : nullptr;
+  const double* xa = ca < ncols ? X + (int64_t)ca * my_side(a).ldx : nullptr;
+  const double* xb = cb < ncols ? X + (int64_t)cb * my_side(a).ldx : nullptr;
   cx<T> x[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) x[e] = load_z<T>(xa, xb, M, tt + TP * e);
-  fft_seq<T, LOGL, E>(x, lds + sl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t1));
+  fft_seq<T, LOGL, E, true>(x, lds + 2 * sl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t1));
   if (ca >= a.ncols_out) return;
   double sa, sb;
   col_scales(a, ca, cb, ncols, sa, sb);
@@ -435,8 +460,8 @@ __global__ __launch_bounds__(512, 4) void k_dst_pass1(DstArgs a) {
   const int64_t M = (int64_t)L1 * L2 / 2;
   const int j1 = tile * TJ + cl;
   const bool valid = j1 <= L1 / 2;
-  const double* xa = X + (int64_t)ca * a.side[blockIdx.y].ldx - 1;
-  const double* xb = cb < ncols ? X + (int64_t)cb * a.side[blockIdx.y].ldx - 1 : nullptr;
+  const double* xa = X + (int64_t)ca * my_side(a).ldx - 1;
+  const double* xb = cb < ncols ? X + (int64_t)cb * my_side(a).ldx - 1 : nullptr;
   cx<T> x[E];
   load_odd<T, E, true>(x, (int64_t)L1 * TP, min(j1, L1 / 2) + L1 * tt, M, [&](int64_t base, unsigned lane) {
     return cx<T>{(T)(xa + base)[lane], xb ? (T)(xb + base)[lane] : T(0)};
@@ -619,7 +644,7 @@ template <typename T, int LOGM>
 __global__ __launch_bounds__(512) void k_dst_bs_single(BsArgs a) {
   constexpr int M = 1 << LOGM, E = 16, TP = M / E;
   constexpr int SEQS = single_seqs(LOGM), SEQ = seq_len(M);
-  __shared__ T lds[SEQS * SEQ];
+  __shared__ __align__(16) T lds[2 * SEQS * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a.d, X, ncols)) return;
@@ -628,21 +653,21 @@ __global__ __launch_bounds__(512) void k_dst_bs_single(BsArgs a) {
   const bool mine = lp < a.npairs;
   const int pair = a.pair0 + lp;
   const int ca = 2 * pair, cb = ca + 1;
-  const double* xa = mine && ca < ncols ? X + (int64_t)ca * a.d.side[blockIdx.y].ldx : nullptr;
-  const double* xb = mine && cb < ncols ? X + (int64_t)cb * a.d.side[blockIdx.y].ldx : nullptr;
+  const double* xa = mine && ca < ncols ? X + (int64_t)ca * my_side(a.d).ldx : nullptr;
+  const double* xb = mine && cb < ncols ? X + (int64_t)cb * my_side(a.d).ldx : nullptr;
   const cx<T>* chirp = reinterpret_cast<const cx<T>*>(a.chirp);
   const cx<T>* bhat = reinterpret_cast<const cx<T>*>(a.bhat);
   const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.t1);
   cx<T> x[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) x[e] = bs_input<T>(xa, xb, a.N, chirp, tt + TP * e);
-  fft_seq<T, LOGM, E>(x, lds + sl * SEQ, tt, tw);
+  fft_seq<T, LOGM, E, true>(x, lds + 2 * sl * SEQ, tt, tw);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const cx<T> v = cmul(x[e], bhat[tt + TP * e]);
     x[e] = {v.x, -v.y};
   }
-  fft_seq<T, LOGM, E>(x, lds + sl * SEQ, tt, tw);
+  fft_seq<T, LOGM, E, true>(x, lds + 2 * sl * SEQ, tt, tw);
   if (!mine || ca >= a.d.ncols_out) return;
   double sa, sb;
   col_scales(a.d, ca, cb, ncols, sa, sb);
@@ -673,8 +698,8 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_pass1(BsArgs a) {
   const int j1 = tile * TJ + cl;
   cx<T> x[E];
   if (FROM_X) {
-    const double* xa = X + (int64_t)ca * a.d.side[blockIdx.y].ldx;
-    const double* xb = cb < ncols ? X + (int64_t)cb * a.d.side[blockIdx.y].ldx : nullptr;
+    const double* xa = X + (int64_t)ca * my_side(a.d).ldx;
+    const double* xb = cb < ncols ? X + (int64_t)cb * my_side(a.d).ldx : nullptr;
     const cx<T>* chirp = reinterpret_cast<const cx<T>*>(a.chirp);
 #pragma unroll
     for (int e = 0; e < E; ++e) x[e] = bs_input<T>(xa, xb, a.N, chirp, j1 + (int64_t)M1 * (tt + TP * e));
@@ -797,8 +822,8 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_odd1(BsArgs a) {
   const unsigned off = min(j1, M1 / 2) + M1 * tt;
   cx<T> x[E];
   if (FROM_X) {
-    const double* xa = X + (int64_t)ca * a.d.side[blockIdx.y].ldx;
-    const double* xb = cb < ncols ? X + (int64_t)cb * a.d.side[blockIdx.y].ldx : nullptr;
+    const double* xa = X + (int64_t)ca * my_side(a.d).ldx;
+    const double* xb = cb < ncols ? X + (int64_t)cb * my_side(a.d).ldx : nullptr;
     const cx<T>* chirp = reinterpret_cast<const cx<T>*>(a.chirp);
     load_odd<T, E, false>(x, (int64_t)M1 * TP, off, valid ? a.N : 0, [&](int64_t base, unsigned lane) {
       const double va = (xa + base - 1)[lane], vb = xb ? (xb + base - 1)[lane] : 0.0;
@@ -914,13 +939,13 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_odd2(BsArgs a) {
 template <int LOGM>
 __global__ __launch_bounds__(256) void k_fft_plain_single(double2* B, const double2* tw) {
   constexpr int M = 1 << LOGM, E = 16, TP = M / E;
-  __shared__ double lds[seq_len(M)];
+  __shared__ __align__(16) double lds[2 * seq_len(M)];
   const int tt = threadIdx.x;
   cx<double>* Bc = reinterpret_cast<cx<double>*>(B);
   cx<double> x[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) x[e] = Bc[tt + TP * e];
-  fft_seq<double, LOGM, E>(x, lds, tt, reinterpret_cast<const cx<double>*>(tw));
+  fft_seq<double, LOGM, E, true>(x, lds, tt, reinterpret_cast<const cx<double>*>(tw));
 #pragma unroll
   for (int e = 0; e < E; ++e) Bc[tt + TP * e] = x[e];
 }
