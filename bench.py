@@ -154,6 +154,9 @@ def kernel_model(w, prec, trace, info, rF):
     wb = 4 if prec == "mixed" else 8           # width of the spectral factors and fibers
     r = info.rank
     passes = trace                              # passes actually computed
+    # rows of the factor products: from n = 65536 on they run on the level above the QR's leaves
+    # (r_max rows per 256)
+    nrow = n if n < 1 << 16 else -(-n // 256) * w.r_max
     out = {}
     # DST: forward U_F, V_F (read FP64, write w); back: read and write the rank live columns
     # (the zero fill of the r_max - r unused output columns is not counted)
@@ -166,8 +169,8 @@ def kernel_model(w, prec, trace, info, rF):
         pI, pJ = len(t["I_pre"]), len(t["J_pre"])
         rk = t["rank"]
         fb += 2 * n * rF * wb + n * (pI + pJ) * wb + 2 * n * wb
-        pb += n * (pI + pJ) * 8 + 2 * n * rk * 8
-        pf += 2 * n * (pI + pJ) * rk
+        pb += nrow * (pI + pJ) * 8 + 2 * nrow * rk * 8
+        pf += 2 * nrow * (pI + pJ) * rk
         # core: Householder QR of the m0 x k0 interpolation rows, triangular inverse, the core
         # product, the SVD of the |J| x |I| core (Golub-Van Loan count 4m^2n + 8mn^2 + 9n^3) and,
         # when the indicator was evaluated, two singular-value-only SVDs (4mn^2 - 4n^3/3)
@@ -180,8 +183,8 @@ def kernel_model(w, prec, trace, info, rF):
                 a, b = max(a, b), min(a, b)
                 cf += 4 * a * b * b - 4 * b ** 3 / 3
     out["fiber"] = {"bytes": fb}
-    pb += 2 * (n * rF * 8 + n * rF * 8)       # warm start: U_-1 = Q U^, V_-1 = Z V~ (rank <= r_F)
-    pf += 2 * 2 * n * rF * rF
+    pb += 2 * (nrow * rF * 8 + nrow * rF * 8)  # warm start: U_-1 = Q U^, V_-1 = Z V~ (rank <= r_F)
+    pf += 2 * 2 * nrow * rF * rF
     out["prod"] = {"bytes": pb, "flops": pf}
     out["core"] = {"flops": cf}
     # thin QRs (Householder, LAPACK counts): factorization 2 n p^2 - 2 p^3 / 3 per side and the
