@@ -296,14 +296,18 @@ static void prof_reduce(lrp_ctx* c) {
 }
 
 // This context's solves keep the rounding of everything up to the core: the column kernels for
-// the thin QRs, full-length FFTs in the transforms to the sine basis at general n. In FP64 at rank
-// caps above 32 the index sets reach the rounding floor of W^: Q(I,:) then has singular values down
-// to 1e-12, and the cross approximation multiplies the rounding of Q by their reciprocals. Two QRs
-// that agree to 1e-15 gave solutions up to 2e-3 apart there (n = 2^20 - 1, 30 bumps, cap 64,
-// identical sets in every pass; 12 seeds, 4 of them above 1e-9), so these solves stay bit for bit
-// what they were. Below, and in mixed precision, the two QRs' solutions agree: 4e-15 at most over 75
-// FP64 solves at caps 16 and 32, 4e-10 over 135 mixed ones.
-static int keep_rounding(const lrp_ctx* c) { return c->precision == LRP_FP64 && c->r_max > 32; }
+// the thin QRs, full-length FFTs in the transforms to the sine basis at general n. In FP64 the index
+// sets reach the rounding floor of W^ wherever the cap or the tolerance lets them outgrow its numerical
+// rank: Q(I,:) then has singular values down to 1e-12, and the cross approximation multiplies the
+// rounding of Q by their reciprocals. Two QRs that agree to 1e-15 gave solutions up to 2e-3 apart at
+// cap 64 (n = 2^20 - 1, 30 bumps, identical sets in every pass), and at cap 32, with 1 or 2 bumps, up
+// to 3.9e-6, once in 20 passes where it had been 5. Neither the cap nor the right-hand side's rank tells
+// beforehand, so the precision decides. With the columns' QR those solves (432 at caps 16, 24 and 32,
+// tolerances 1e-10 and 1e-14) move by 5e-15 at most when the steps from the core on round otherwise.
+// In mixed precision the 1e-7 of the fibers keeps Q(I,:) clear of it: 3e-9 at most between the two QRs
+// over 360 such solves at caps 8 to 64. What the columns' QR costs: n = 255, cap 16, 4 % of the solve;
+// n = 4096, cap 32, 6 %.
+static int keep_rounding(const lrp_ctx* c) { return c->precision == LRP_FP64; }
 
 // Pass k up to the stop decision: the set update from the previous candidates, fibers, the
 // two thin QRs, the core, the factor products, rho and the indicator.
