@@ -184,8 +184,11 @@ __host__ __device__ constexpr int seq_len(int P) { return P + P / 16 + 1; }
 // share a CU where whole complex values and 160 VGPRs left one (8 waves); their memory phases cover
 // each other's barriers. FP64, both passes: 56 -> 43 us at n = 65535, 64 columns (134 MB in four
 // passes over memory); 89 -> 67 at n = 262143, 30 columns; 394 -> 372 at n = 2^20 - 1, 30 columns.
-// WHOLE: complex values at once, half the barriers, for the one-pass transforms, whose few small
-// workgroups wait on nothing else.
+// WHOLE: complex values at once, half the barriers: for the one-pass transforms, whose few small
+// workgroups wait on nothing else, and in Bluestein's full-length passes up to kWholeFull, where two
+// workgroups' whole values fit a CU as well.
+constexpr int kWholeFull = 7;
+
 template <typename T, int E, int P, int R, int LS, bool WHOLE>
 __device__ __forceinline__ void stage(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
   constexpr int TP = P / E, NB = E / R;
@@ -682,8 +685,9 @@ __global__ __launch_bounds__(512) void k_dst_bs_single(BsArgs a) {
 template <typename T, int LOG2, bool FROM_X>
 __global__ __launch_bounds__(512, 4) void k_dst_bs_pass1(BsArgs a) {
   constexpr int M2 = 1 << LOG2, E = 16, TP = M2 / E;
-  constexpr int TJ = tile1_of<T>(LOG2), SEQ = seq_len(M2);
-  __shared__ T lds[TJ * SEQ];
+  constexpr bool WHOLE = LOG2 <= kWholeFull;
+  constexpr int TJ = tile1_of<T>(LOG2), SEQ = (WHOLE ? 2 : 1) * seq_len(M2);
+  __shared__ __align__(16) T lds[TJ * SEQ];
   const double* X = nullptr;
   int ncols = 0;
   if (!a.plain && !dst_resolve(a.d, X, ncols)) return;
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_pass1(BsArgs a) {
 #pragma unroll
     for (int e = 0; e < E; ++e) x[e] = Bp[j1 + (int64_t)M1 * (tt + TP * e)];
   }
-  fft_seq<T, LOG2, E>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
+  fft_seq<T, LOG2, E, WHOLE>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
   const cx<T>* thi = reinterpret_cast<const cx<T>*>(a.t1);  // W_M^{M2 h} = W_M1^h
   const cx<T>* tlo = reinterpret_cast<const cx<T>*>(a.tl);  // W_M^b, b < M2
   cx<T>* S = reinterpret_cast<cx<T>*>(a.S) + (int64_t)(pair - a.pair0 + a.npairs * blockIdx.y) * M2 * a.s1;
@@ -726,9 +730,10 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_pass1(BsArgs a) {
 template <typename T, int LOG1, bool TO_DST>
 __global__ __launch_bounds__(512, 4) void k_dst_bs_pass2(BsArgs a) {
   constexpr int M1 = 1 << LOG1, E = 16, TP = M1 / E;
-  constexpr int TK = tile2_of<T>(LOG1), SEQ = seq_len(M1);
-  constexpr int NLDS = lds_pass2(LOG1, TK, 1);
-  __shared__ T lds[NLDS];
+  constexpr bool WHOLE = LOG1 <= kWholeFull;
+  constexpr int TK = tile2_of<T>(LOG1), SEQ = (WHOLE ? 2 : 1) * seq_len(M1);
+  constexpr int NLDS = (WHOLE ? 2 : 1) * lds_pass2(LOG1, TK, 1);
+  __shared__ __align__(16) T lds[NLDS];
   const double* X = nullptr;
   int ncols = 0;
   if (!a.plain && !dst_resolve(a.d, X, ncols)) return;
@@ -750,7 +755,7 @@ __global__ __launch_bounds__(512, 4) void k_dst_bs_pass2(BsArgs a) {
     cx<T> x[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) x[e] = S[(int64_t)(k0 + kl) * a.s1 + tt + TP * e];
-    fft_seq<T, LOG1, E>(x, lds + kl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t1));
+    fft_seq<T, LOG1, E, WHOLE>(x, lds + kl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t1));
     stage_out<T, M1, TK, false>(x, lds, tt, kl, z);
   }
   double sa = 1.0, sb = 1.0;
@@ -1193,10 +1198,11 @@ static int bs_pass1(int logL2, int M1, int np, const BsArgs& b, hipStream_t s) {
                dim3(tj * ((1 << LG) / 16)), 0, s, b);                                                           \
     return launch_status();                                                                                     \
   }
-  switch (logL2) {
-    LRP_BSP1(6) LRP_BSP1(7) LRP_BSP1(8) LRP_BSP1(9) LRP_BSP1(10) LRP_BSP1(11) LRP_BSP1(12)
-    default: return LRP_EINVAL;
+  switch (logL2) { LRP_BSP1(6) LRP_BSP1(7) }
+  if constexpr (std::is_same<T, double>::value) {  // FP32: up to kFullLog32 only
+    switch (logL2) { LRP_BSP1(8) LRP_BSP1(9) LRP_BSP1(10) LRP_BSP1(11) LRP_BSP1(12) }
   }
+  return LRP_EINVAL;
 #undef LRP_BSP1
 }
 
@@ -1209,10 +1215,11 @@ static int bs_pass2(int logL1, int M2, int np, const BsArgs& b, hipStream_t s) {
                dim3(tk * ((1 << LG) / 16)), 0, s, b);                                                           \
     return launch_status();                                                                                     \
   }
-  switch (logL1) {
-    LRP_BSP2(7) LRP_BSP2(8) LRP_BSP2(9) LRP_BSP2(10) LRP_BSP2(11) LRP_BSP2(12)
-    default: return LRP_EINVAL;
+  switch (logL1) { LRP_BSP2(7) LRP_BSP2(8) }
+  if constexpr (std::is_same<T, double>::value) {  // as in bs_pass1
+    switch (logL1) { LRP_BSP2(9) LRP_BSP2(10) LRP_BSP2(11) LRP_BSP2(12) }
   }
+  return LRP_EINVAL;
 #undef LRP_BSP2
 }
 
@@ -1314,13 +1321,10 @@ static int bs_launch(const DstPlan& p, BsArgs b, hipStream_t s) {
     return LRP_EINVAL;
   }
   if (b.d.full_bluestein) {
-    if constexpr (std::is_same<T, double>::value) {  // only FP64 transforms ask for it
-      TRY_DST((bs_pass1<T, true>(p.logL2, M1, np, b, s)));    // DFT of a = z c
-      TRY_DST((bs_pass2<T, false>(p.logL1, M2, np, b, s)));   // conj(. bhat) into B
-      TRY_DST((bs_pass1<T, false>(p.logL2, M1, np, b, s)));   // DFT of B
-      return bs_pass2<T, true>(p.logL1, M2, np, b, s);         // c_k conj(.)/M: the DST outputs
-    }
-    return LRP_EINVAL;
+    TRY_DST((bs_pass1<T, true>(p.logL2, M1, np, b, s)));    // DFT of a = z c
+    TRY_DST((bs_pass2<T, false>(p.logL1, M2, np, b, s)));   // conj(. bhat) into B
+    TRY_DST((bs_pass1<T, false>(p.logL2, M1, np, b, s)));   // DFT of B
+    return bs_pass2<T, true>(p.logL1, M2, np, b, s);         // c_k conj(.)/M: the DST outputs
   }
   b.s1odd = M1 / 2 + 8;
   TRY_DST((bs_odd1<T, true>(p.logL2, M1, np, b, s)));    // DFT of a = z c
@@ -1370,17 +1374,31 @@ static int dst_rounds(const DstPlan& p, DstArgs a, int npairs, int bp, bool fp32
   return launch_status();
 }
 
+// Transforms of M <= 2^15 (2^14 in FP64) points that together are at most 1 MB a buffer, in one round,
+// take the full-length FFTs: such a launch is bound by latency, and a pass over the odd half, with its
+// mirrored elements and their branches, is about 1 us longer (four passes, full length against odd half:
+// n = 1024, 8 columns, FP32 26.1 against 30.4 us, FP64 28.5 against 31.6; n = 3000, 4 columns, FP32 27.7
+// against 30.9, FP64 30.8 against 31.5). Above, the halved work decides: n = 1024, 32 columns, FP64, two
+// rounds of the full length 57 against 31, n = 4096, one column, FP64, 32.2 against 30.3; at the line, n =
+// 3000, 8 columns, FP64, they are the same.
+constexpr int kFullLog64 = 14, kFullLog32 = 15;
+static bool small_bluestein(const DstPlan& p, int pairs, bool fp32) {
+  return p.logM <= (fp32 ? kFullLog32 : kFullLog64) && pairs <= p.batch_pairs * (fp32 ? 2 : 1) &&
+         ((int64_t)pairs << p.logM) * (fp32 ? 8 : 16) <= int64_t(1) << 20;
+}
+
 int dst_launch(const DstPlan& p, DstArgs a, bool fp32, hipStream_t s) {
   const int npairs = (a.ncols_out + 1) / 2;
   if (npairs <= 0) return LRP_OK;
   if (npairs > p.max_pairs) return LRP_EINVAL;
   for (DstSide& d : a.side) d.outscale *= 1.0 / std::sqrt(2.0 * (double)(p.n + 1));
+  if (p.bluestein && p.four_step && small_bluestein(p, npairs * a.nsides, fp32)) a.full_bluestein = 1;
   // Pairs per round, by the work buffers: FP32 values take half the bytes, the odd half of Bluestein's
   // transforms takes half of them again.
   int bp = p.max_pairs;  // one pass: no buffers
   if (p.four_step) {
     bp = p.batch_pairs;
-    if (fp32 && !(p.bluestein && a.full_bluestein)) bp *= 2;
+    if (fp32) bp *= 2;
     if (p.bluestein && !a.full_bluestein) bp *= 2;
   }
   // Both sets go in one launch where one round holds them (always in one-pass transforms), else one
