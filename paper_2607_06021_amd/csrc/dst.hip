@@ -387,17 +387,25 @@ __host__ __device__ constexpr int tile2_for(int log1, int esz, int cap, int lds_
   while (t > 1 && (lds_pass2(log1, t, esz) > lds_max || t * ((1 << log1) / 16) > 512)) t >>= 1;
   return t;
 }
-// Column tiles of the four-step passes: the widest that fit (CAP = 0), or at most CAP columns --
-// narrow tiles for launches that would otherwise leave CUs idle (few column pairs). A column's
-// transform is the same whatever tile it sits in.
+// Column tiles of the four-step passes: the widest that fit (CAP = 0), or at most CAP columns and in
+// FP64 at most half the widest -- narrow tiles for launches that would otherwise leave CUs idle (few
+// column pairs). In FP64 a pair of n = 524287 makes 65 workgroups of the widest tile in pass 1, 129 of
+// half of it: 31.7 -> 27.8 us for the pair. FP32 keeps the widest: half of it is faster there (26.7 -> 23.8)
+// and slower at n = 2^21 - 1 (54 -> 58). A column's transform is the same whatever tile it sits in.
 constexpr int kNarrow1 = 8, kNarrow2 = 4;
+__host__ __device__ constexpr int narrow_tile(int wide, int cap, int esz) {
+  const int half = esz == 8 && wide > 1 ? wide / 2 : wide;
+  return half < cap ? half : cap;
+}
 template <typename T, int CAP = 0>
 __host__ __device__ constexpr int tile1_of(int log2) {
-  return tile1_for(log2, (int)sizeof(T), CAP ? CAP : 32, kLdsTile);
+  const int wide = tile1_for(log2, (int)sizeof(T), 32, kLdsTile);
+  return CAP ? narrow_tile(wide, CAP, (int)sizeof(T)) : wide;
 }
 template <typename T, int CAP = 0>
 __host__ __device__ constexpr int tile2_of(int log1) {
-  return tile2_for(log1, (int)sizeof(T), CAP ? CAP : 16, kLdsTile);
+  const int wide = tile2_for(log1, (int)sizeof(T), 16, kLdsTile);
+  return CAP ? narrow_tile(wide, CAP, (int)sizeof(T)) : wide;
 }
 
 // ---------------------------------------------------------------- L <= 4096: one pass
