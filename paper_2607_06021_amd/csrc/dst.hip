@@ -185,9 +185,17 @@ __host__ __device__ constexpr int seq_len(int P) { return P + P / 16 + 1; }
 // each other's barriers. FP64, both passes: 56 -> 43 us at n = 65535, 64 columns (134 MB in four
 // passes over memory); 89 -> 67 at n = 262143, 30 columns; 394 -> 372 at n = 2^20 - 1, 30 columns.
 // WHOLE: complex values at once, half the barriers: for the one-pass transforms, whose few small
-// workgroups wait on nothing else, and in Bluestein's full-length passes up to kWholeFull, where two
-// workgroups' whole values fit a CU as well.
+// workgroups wait on nothing else; in Bluestein's full-length passes up to kWholeFull, where two
+// workgroups' whole values fit a CU as well; and in the power-of-two passes' wide tiles from kWholePass1/2
+// up. Those tiles are 8 columns or fewer, and FP32's whole values fit a CU twice, so that halving them made
+// four workgroups of two: more of the narrow pieces of lines in flight than the XCD's L2 joins. FP32, us,
+// components against whole: n = 2^20 - 1, 16 columns 168 and 157, n = 2^21 - 1, 64 columns 1591 and 1552;
+// in FP64, 64 columns of 2^21 - 1, 1832 and 1768 (whole in pass 1), 16 of 2^22 - 1, 1130 and 1031.
 constexpr int kWholeFull = 7;
+template <typename T>
+constexpr int kWholePass1 = sizeof(T) == 4 ? 10 : 11;
+template <typename T>
+constexpr int kWholePass2 = sizeof(T) == 4 ? 11 : 12;
 
 template <typename T, int E, int P, int R, int LS, bool WHOLE>
 __device__ __forceinline__ void stage(cx<T> (&x)[E], T* lds, int tt, const cx<T>* __restrict__ tw) {
@@ -387,6 +395,15 @@ __host__ __device__ constexpr int tile2_for(int log1, int esz, int cap, int lds_
   while (t > 1 && (lds_pass2(log1, t, esz) > lds_max || t * ((1 << log1) / 16) > 512)) t >>= 1;
   return t;
 }
+// Length of a second pass with tiles of two columns. They write 16-byte pieces of the output's lines, whose
+// neighbours come from the next workgroups: more than half of a CU's LDS, so that one workgroup runs per CU,
+// and each piece stored as it is read back, so that the lines in the making fit the XCD's L2 (n = 2^22 - 1,
+// us a launch, with two per CU and all pieces at the end against this: FP32 145 and 120, FP64 89 and 82).
+constexpr int kTwoColLog = 12;
+template <typename T>
+__host__ __device__ constexpr int lds_two_col() {
+  return (kLdsTile + 1024) / (int)sizeof(T);
+}
 // Column tiles of the four-step passes: the widest that fit (CAP = 0), or at most CAP columns and in
 // FP64 at most half the widest -- narrow tiles for launches that would otherwise leave CUs idle (few
 // column pairs). In FP64 a pair of n = 524287 makes 65 workgroups of the widest tile in pass 1, 129 of
@@ -452,8 +469,9 @@ __device__ __forceinline__ int xcd_order(int b, int nb) {
 template <typename T, int LOG2, int CAP = 0>
 __global__ __launch_bounds__(512, 4) void k_dst_pass1(DstArgs a) {
   constexpr int L2 = 1 << LOG2, E = 16, TP = L2 / E;
-  constexpr int TJ = tile1_of<T, CAP>(LOG2), SEQ = seq_len(L2);
-  __shared__ T lds[TJ * SEQ];
+  constexpr bool WHOLE = CAP == 0 && LOG2 >= kWholePass1<T>;
+  constexpr int TJ = tile1_of<T, CAP>(LOG2), SEQ = (WHOLE ? 2 : 1) * seq_len(L2);
+  __shared__ __align__(16) T lds[TJ * SEQ];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
@@ -477,7 +495,7 @@ __global__ __launch_bounds__(512, 4) void k_dst_pass1(DstArgs a) {
   load_odd<T, E, true>(x, (int64_t)L1 * TP, min(j1, L1 / 2) + L1 * tt, M, [&](int64_t base, unsigned lane) {
     return cx<T>{(T)(xa + base)[lane], xb ? (T)(xb + base)[lane] : T(0)};
   });
-  fft_seq<T, LOG2, E>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
+  fft_seq<T, LOG2, E, WHOLE>(x, lds + cl * SEQ, tt, reinterpret_cast<const cx<T>*>(a.t2));
   if (!valid) return;
   const cx<T>* thi = reinterpret_cast<const cx<T>*>(a.t1);  // W_L^{L2 h} = W_L1^h
   const cx<T>* tlo = reinterpret_cast<const cx<T>*>(a.tl);  // W_L^b, b < L2
@@ -530,9 +548,12 @@ __device__ __forceinline__ void stage_out(const cx<T> (&x)[16], T* lds, int tt, 
 template <typename T, int LOG1, int CAP = 0>
 __global__ __launch_bounds__(512, 4) void k_dst_pass2(DstArgs a) {
   constexpr int L1 = 1 << LOG1, E = 16, TP = L1 / E;
-  constexpr int TK = tile2_of<T, CAP>(LOG1), SEQ = seq_len(L1);
-  constexpr int NLDS = lds_pass2(LOG1, TK, 1);
-  __shared__ T lds[NLDS];
+  constexpr bool WHOLE = CAP == 0 && LOG1 >= kWholePass2<T>;
+  constexpr int TK = tile2_of<T, CAP>(LOG1), SEQ = (WHOLE ? 2 : 1) * seq_len(L1);
+  constexpr bool TWO_COL = WHOLE && LOG1 == kTwoColLog;
+  constexpr int kNeed = (WHOLE ? 2 : 1) * lds_pass2(LOG1, TK, 1);
+  constexpr int NLDS = TWO_COL && kNeed < lds_two_col<T>() ? lds_two_col<T>() : kNeed;
+  __shared__ __align__(16) T lds[NLDS];
   const double* X;
   int ncols;
   if (!dst_resolve(a, X, ncols)) return;
@@ -551,23 +572,23 @@ __global__ __launch_bounds__(512, 4) void k_dst_pass2(DstArgs a) {
   col_scales(a, ca, cb, ncols, sa, sb);
   // staged entry g: kl = g % TK, row = g / TK; rows < L1/2 hold Z[k2 + L2 row] of column
   // k2 = k0 + kl, rows L1/2 + m hold Z[(L2 - k2) + L2 m] (already negated).
-  auto write_out = [&](const cx<T>(&z)[16]) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int g = threadIdx.x + nthreads * i;
-      const int kl = g % TK, row = g / TK;
-      const int k2 = k0 + kl;
-      int64_t k;
-      if (row < L1 / 2) {
-        if (k2 > L2 / 2) continue;
-        k = k2 + (int64_t)L2 * row;
-        if (k == 0) continue;
-      } else {
-        if (k2 == 0 || k2 >= L2 / 2) continue;
-        k = (L2 - k2) + (int64_t)L2 * (row - L1 / 2);
-      }
-      put_pair<T>(a, ca, cb, ncols, k, z[i], sa, sb);
+  auto put = [&](int g, cx<T> Z) __attribute__((always_inline)) {
+    const int kl = g % TK, row = g / TK;
+    const int k2 = k0 + kl;
+    int64_t k;
+    if (row < L1 / 2) {
+      if (k2 > L2 / 2) return;
+      k = k2 + (int64_t)L2 * row;
+      if (k == 0) return;
+    } else {
+      if (k2 == 0 || k2 >= L2 / 2) return;
+      k = (L2 - k2) + (int64_t)L2 * (row - L1 / 2);
     }
+    put_pair<T>(a, ca, cb, ncols, k, Z, sa, sb);
+  };
+  auto write_out = [&](const cx<T>(&z)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) put(threadIdx.x + nthreads * i, z[i]);
   };
   cx<T> z[16];
   if (ca >= ncols) {  // both columns zero
@@ -601,9 +622,22 @@ __global__ __launch_bounds__(512, 4) void k_dst_pass2(DstArgs a) {
     }
     x[e] = v;
   }
-  fft_seq<T, LOG1, E>(x, lds + kl * SEQ, tt, t1);
-  stage_out<T, L1, TK, true>(x, lds, tt, kl, z);
-  write_out(z);
+  fft_seq<T, LOG1, E, WHOLE>(x, lds + kl * SEQ, tt, t1);
+  if constexpr (TWO_COL) {
+    cx<T>* out = reinterpret_cast<cx<T>*>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int k1 = tt + TP * e;
+      out[opad((k1 < L1 / 2 ? k1 : L1 / 2 + (L1 - 1 - k1)) * TK + kl)] = k1 < L1 / 2 ? x[e] : cneg(x[e]);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int g = threadIdx.x; g < L1 * TK; g += nthreads) put(g, out[opad(g)]);
+  } else {
+    stage_out<T, L1, TK, true>(x, lds, tt, kl, z);
+    write_out(z);
+  }
 }
 
 // ----------------------------------------------------------------------------------------

@@ -1,7 +1,7 @@
 """General-n DSTs on both sides of the line between full-length and odd-half transforms (at most
 1 MB of transform data a buffer, M <= 2^14 points in FP64 and 2^15 in FP32): the last column count of
 the one and the first of the other per length, and power-of-two sizes with so few columns that the
-narrowest tiles run. Against the oracle, with the tolerances of the other DST tests (a few eps per
+narrowest tiles run, up to the largest, whose wide tiles are two columns. Against the oracle, with the tolerances of the other DST tests (a few eps per
 butterfly level)"""
 import math
 
@@ -33,7 +33,8 @@ def test_dst_at_the_line(n, edge64, edge32):
                 assert err <= tol, (prec, cols, err)
 
 
-@pytest.mark.parametrize("n,cols", [(262143, 1), (524287, 1), (524287, 3), (1048575, 2)])
+@pytest.mark.parametrize("n,cols", [(262143, 1), (524287, 1), (524287, 3), (1048575, 2), (1048575, 16),
+                                    (2097151, 4), (4194303, 3), (8388607, 2)])
 def test_dst_few_columns(n, cols):
     import torch
 
