@@ -60,7 +60,6 @@ typedef double wy4 __attribute__((ext_vector_type(4)));
 constexpr int kWyThreads = 256;           // 4 waves, 16 columns each
 constexpr int kPanel = 16;                // columns per panel
 constexpr int kVLd = kPanel + 1;          // LDS row stride of a panel (odd: the transposed reads spread over the banks)
-constexpr int kTiles = kTsqrRows / 16;    // 16-row tiles of a block
 
 __device__ __forceinline__ wy4 mfma4(double a, double b, wy4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -511,13 +510,17 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
 // in registers throughout and needs nothing of the other waves'; the panels are staged through two
 // LDS buffers (the next one's loads in flight behind the products), one barrier per panel.
 //
-// Bound by the matrix cores where the chip is full (2 p products of 16 x 16 x 4 per panel and wave, 72
-// cycles each) and by the chain of the panels where it is not. No triangular solve and no V^T V: the
-// panels' T factors come from the factorization. Against the compact WY form of tsqr.hip: a level of
-// few blocks 18 -> 13 us at p = 32, 26 -> 14 us at p = 45, 38 -> 20 us at p = 64; the leaves of
-// n = 2^20 - 1 at p = 64 569 -> 405 us. Dealing rows instead of columns to the waves (the sums of
+// Bound by the matrix cores where the chip is full (132 products of 16 x 16 x 4 per leaf panel and wave:
+// 64 for V^T Y, 4 for T W, 64 for the update; 84 for the first panel applied, and fewer where tile
+// classes are not in use; 72 cycles each) and by the chain of the panels where it is not. No triangular
+// solve and no V^T V: the panels' T factors come from the factorization. Against the compact WY form of
+// tsqr.hip: a level of few blocks 18 -> 13 us at p = 32, 26 -> 14 us at p = 45, 38 -> 20 us at p = 64; the
+// leaves of n = 2^20 - 1 at p = 64 569 -> 405 us. Dealing rows instead of columns to the waves (the sums of
 // V^T Y then cross the waves, two barriers per panel) was slower: 593 us.
-template <class Src>
+//
+// NT: the tiles that can hold rows of a block, 16 or, where a level is one short block, 4 or 8 (see
+// tsqr_panel_apply).
+template <class Src, int NT>
 __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_tsqr_panel_apply(Src in) {
   const PanelApplyArgs& a = kernel_args<PanelApplyArgs>(in);
   const int side = blockIdx.y;
@@ -539,7 +542,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
   const int sr = t >> 4, scol = t & 15;  // staging: row sr of every tile, column scol
 
   // panel P of the reflectors as stored: item I is row 16 I + sr (tile I)
-  double raw[kTiles];
+  double raw[NT];
   auto fetch = [&](int P) {
     const int cw = min(kPanel, p - kPanel * P);
     const double* V = Vb + (int64_t)kPanel * P * nr + min(scol, cw - 1);
@@ -548,13 +551,13 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     for (int k = 0; k < 4; ++k)
       if (cls >> k & 1) {  // uniform
 #pragma unroll
-        for (int I = k; I < kTiles; I += 4) raw[I] = V[min(16 * I + sr, nr - 1) * cw];
+        for (int I = k; I < NT; I += 4) raw[I] = V[min(16 * I + sr, nr - 1) * cw];
       }
   };
   fetch(pt - 1);
-  wy4 y[kTiles];
+  wy4 y[NT];
 #pragma unroll
-  for (int I = 0; I < kTiles; ++I) y[I] = wy4{0.0, 0.0, 0.0, 0.0};
+  for (int I = 0; I < NT; ++I) y[I] = wy4{0.0, 0.0, 0.0, 0.0};
   {
     const double* T = a.T[side];
     double tp[16];
@@ -584,7 +587,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         vs[16 * k * kVLd] = k < P ? 0.0 : k > P || sr > scol ? v0 : sr == scol ? 1.0 : 0.0;
         if (k == P) ts[sr * kVLd + scol] = sr <= scol ? v0 : 0.0;
 #pragma unroll
-        for (int I = k + 4; I < kTiles; I += 4) {
+        for (int I = k + 4; I < NT; I += 4) {
           keep_loaded(raw[I]);
           vs[16 * I * kVLd] = 16 * I + sr < nr && scol < cw ? raw[I] : 0.0;
         }
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
       for (int k = 0; k < 4; ++k)
         if (cls >> k & 1) {
 #pragma unroll
-          for (int I = k; I < kTiles; I += 4) {
+          for (int I = k; I < NT; I += 4) {
             if (I >= 4 && P == pt - 1) break;  // uniform
 #pragma unroll
             for (int v = 0; v < 4; ++v) W = mfma4(vs[(16 * I + 4 * v + g) * kVLd + c], y[I][v], W);
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
       for (int k = 0; k < 4; ++k)
         if (cls >> k & 1) {
 #pragma unroll
-          for (int I = k; I < kTiles; I += 4)
+          for (int I = k; I < NT; I += 4)
 #pragma unroll
             for (int s = 0; s < 4; ++s) y[I] = mfma4(vs[(16 * I + c) * kVLd + 4 * s + g], Z[s], y[I]);
         }
@@ -625,7 +628,7 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     double* Yr = a.Y[side] + row0 + (int64_t)(kPanel * w) * a.ldy + lane;
     const int cols = min(kPanel, oc - kPanel * w);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < NT / 4; ++b) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) st[(4 * e + g) * kVLd + c] = y[4 * b + (e >> 2)][e & 3];
       double o[kPanel];
@@ -693,8 +696,20 @@ int tsqr_panel_apply(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOut&
     a.T[q] = o.T[q];
     a.Y[q] = o.Y[q];
   }
-  LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_panel_apply<PanelApplyArgs>, k_tsqr_panel_apply<GroupRef>,
-               dim3(o.sel.pick ? p.pmax : lv.nblocks, io.nsides), dim3(kWyThreads), 0, s, a);
+  // A level of one block of at most 64 (128) rows, a small matrix or a tree's root, is a chain on its own
+  // and need not multiply the tiles past its rows: 64 x 33 59 -> 49 us, 257 x 17 (its root of 34 rows) 61 ->
+  // 56. The choice inside the kernel made it three times as long, and levels of more blocks, short last
+  // one or not, 1 to 3 us slower each.
+#define LRP_APPLY(NT)                                                                                           \
+  LRP_LAUNCH_G(K_TSQR_APPLY, (k_tsqr_panel_apply<PanelApplyArgs, NT>), (k_tsqr_panel_apply<GroupRef, NT>),        \
+               dim3(o.sel.pick ? p.pmax : lv.nblocks, io.nsides), dim3(kWyThreads), 0, s, a)
+  if (lv.nblocks > 1 || lv.rows > 128)
+    LRP_APPLY(16);
+  else if (lv.rows > 64)
+    LRP_APPLY(8);
+  else
+    LRP_APPLY(4);
+#undef LRP_APPLY
   return launch_status();
 }
 
