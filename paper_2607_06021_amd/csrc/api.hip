@@ -1063,6 +1063,14 @@ int lrp_set_index_sets(lrp_ctx* c, int32_t npasses, const int64_t* I, const int3
   return LRP_OK;
 }
 
+// For the library's own tests (not in lrp.h): lrp_tsqr and the FP64 lrp_dst1 of this context run the kernels
+// that only FP64 solves take otherwise (keep_rounding), so that these can be tested by themselves.
+int lrp_test_solve_kernels(lrp_ctx* c, int32_t enabled) {
+  if (!c) return LRP_EINVAL;
+  c->solve_kernels = enabled != 0;
+  return LRP_OK;
+}
+
 int lrp_destroy(lrp_ctx* c) {
   if (!c) return LRP_OK;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
@@ -1080,6 +1088,7 @@ int lrp_dst1(lrp_ctx* c, int32_t ncols, const double* X, int64_t ldx, double* Y,
   a.nsides = 1;
   a.ncols = ncols;
   a.ncols_out = ncols;
+  a.full_bluestein = c->solve_kernels && precision == LRP_FP64;
   a.side[0] = DstSide{X, nullptr, ldx, Y, nullptr, ldy, scale, mul};
   return dst_launch(c->dst, a, precision == LRP_MIXED, c->stream);
 }
@@ -1099,6 +1108,7 @@ int lrp_tsqr(lrp_ctx* c, int32_t ncols, const double* A, int64_t lda, double* Q,
   io.ldx = lda;
   io.Q[0] = Q;
   io.ldq = ldq;
+  io.columns = c->solve_kernels;
   TRY(tsqr_run(c->tsqr, io, c->stream));
   if (hipMemcpy2DAsync(R, sizeof(double) * ldr, tsqr_R(c->tsqr, 0), sizeof(double) * c->r_max,
                        sizeof(double) * ncols, ncols, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)

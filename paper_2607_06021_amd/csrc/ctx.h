@@ -60,6 +60,7 @@ struct lrp_ctx {
   bool fiber_narrow = false;         // the right-hand side of the current solve has rank <= 32
   bool use_graphs = true;
   bool solved = false;
+  bool solve_kernels = false;        // lrp_test_solve_kernels
   // optional per-kernel timing (LRP_FLAG_PROFILE): events recorded before every launch
   bool profile = false;
   std::vector<hipEvent_t> prof_ev;
