@@ -195,8 +195,10 @@ struct FactorShared {
 // (alpha - beta) + x_c(pivot): right of J the dot product of the update, left of J (whose
 // registers hold finished reflectors) v_J . v_c, from which T follows. Every wave adds the four
 // waves' parts in the same order and goes on by itself with the same bits. The update takes the
-// scaled v_J (the one extra product per register), so that of two exactly proportional columns
-// that are one large entry (the fibers of sine modes) nothing of that entry is left over.
+// scaled v_J (one extra product per register, 4 % of the time): of exactly proportional columns that are
+// one large entry (the fibers of sine modes) a block then keeps nothing of that entry in a third to all
+// of the columns and up to 1 eps in the others (the column kernels of tsqr.hip in none); the unscaled one
+// always leaves some, unless the ratio is a power of two.
 //
 // With h = sqrt(alpha^2 + |x_tail|^2) and s = sign(alpha): beta = -s h, tau = (beta - alpha) /
 // beta = 1 + |alpha| / h and 1 / (alpha - beta) = s / (|alpha| + h), so one reciprocal square root
