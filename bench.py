@@ -188,12 +188,19 @@ def kernel_model(w, prec, trace, info, rF):
     out["prod"] = {"bytes": pb, "flops": pf}
     out["core"] = {"flops": cf}
     # thin QRs (Householder, LAPACK counts): factorization 2 n p^2 - 2 p^3 / 3 per side and the
-    # same again to form the explicit Q; the warm start factors U^, V^ (p = r_F)
-    qf = 2 * (2 * n * rF ** 2 - 2 * rF ** 3 / 3)
+    # same again to form the explicit Q; the warm start factors U^, V^ (p = r_F). From n = 65536 on Q
+    # is formed above the leaves only (nrow rows) and in the blocks of 256 rows that hold the other
+    # side's indices, and the leaves turn the product's rank columns into the iterate's (2 n p r).
+    qr = lambda m, p: 2 * m * p ** 2 - 2 * p ** 3 / 3
+    sides = [(rF, 0, rF)] * 2  # columns, picked rows, rank
     for t in passes:
-        for pp in (len(t["I_pre"]), len(t["J_pre"])):
-            qf += 2 * n * pp ** 2 - 2 * pp ** 3 / 3
-    out["tsqr"] = {"flops": qf}
+        pI, pJ = len(t["I_pre"]), len(t["J_pre"])
+        sides += [(pJ, pI, t["rank"]), (pI, pJ, t["rank"])]
+    out["tsqr_factor"] = {"flops": sum(qr(n, p) for p, _, _ in sides)}
+    if n < 1 << 16:
+        out["tsqr_apply"] = {"flops": out["tsqr_factor"]["flops"]}
+    else:
+        out["tsqr_apply"] = {"flops": sum(qr(nrow, p) + picked * qr(256, p) + 2 * n * p * r for p, picked, r in sides)}
     # rho (passes where it was evaluated): M = A^T B (pass a), then Y = B - A M and Y^T Y (pass b)
     ra = rb = 0.0
     prev = None
@@ -237,9 +244,8 @@ def rooflines(w, prec, prof, trace, info, rF):
                 "alg_flops_per_launch": round(flops / max(launches, 1))}
 
     res["core"] = alu(m["core"]["flops"], *t("k_core"), "k_core (one workgroup)")
-    # the factorization and the formation of Q each carry the Householder count
-    res["tsqr_factor"] = alu(m["tsqr"]["flops"], *t("k_tsqr_factor"), "k_tsqr_factor (all tree levels)")
-    res["tsqr_apply"] = alu(m["tsqr"]["flops"], *t("k_tsqr_apply"), "k_tsqr_apply (all tree levels)")
+    res["tsqr_factor"] = alu(m["tsqr_factor"]["flops"], *t("k_tsqr_factor"), "k_tsqr_factor (all tree levels)")
+    res["tsqr_apply"] = alu(m["tsqr_apply"]["flops"], *t("k_tsqr_apply"), "k_tsqr_apply (all tree levels)")
     res["rho_a"] = alu(m["rho_a"]["flops"], *t("k_rho_a"), "k_rho_a")
     res["rho_b"] = alu(m["rho_b"]["flops"], *t("k_rho_b"), "k_rho_b")
     return res
