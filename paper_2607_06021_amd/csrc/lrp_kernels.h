@@ -184,6 +184,18 @@ struct TsqrIO {
   int columns;         // 1: the column kernels of tsqr.hip, else the panel kernels (tsqr_panel.hip)
 };
 
+typedef double wy4 __attribute__((ext_vector_type(4)));
+
+// An empty asm statement that takes a loaded value as input and output: the load must then
+// complete unconditionally before it, so a following select on a lane condition cannot be
+// turned into a branch around the load (which would serialise the loads, each with its own wait).
+__device__ inline void keep_loaded(double& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void keep_loaded(float& v) { asm volatile("" : "+v"(v)); }
+
+__device__ inline int side_cols(const DevState* st, const int* fixed, int side) {
+  return st ? st->ncols[side] : fixed[side];
+}
+
 // What a launch of Q's formation covers.
 struct ApplySel {
   int pick;    // 1: only the blocks that hold the rows Ipre (side 0) and Jpre (side 1)

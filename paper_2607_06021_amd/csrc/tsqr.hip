@@ -18,7 +18,6 @@
 
 namespace lrp {
 
-
 struct FactorArgs {
   const DevState* st;
   int ncols[2];
@@ -50,16 +49,6 @@ struct ApplyArgs {
   int64_t ldy;
   ApplySel sel;
 };
-
-// An empty asm statement that takes a loaded value as input and output: the load must then
-// complete unconditionally before it, so a following select on a lane condition cannot be
-// turned into a branch around the load (which would serialise the loads, each with its own wait).
-__device__ inline void keep_loaded(double& v) { asm volatile("" : "+v"(v)); }
-__device__ inline void keep_loaded(float& v) { asm volatile("" : "+v"(v)); }
-
-__device__ inline int side_cols(const DevState* st, const int* fixed, int side) {
-  return st ? st->ncols[side] : fixed[side];
-}
 
 // Sum over the 16 lanes of a DPP row (lanes 16q .. 16q+15); every lane gets the total.
 __device__ inline double row16_sum(double x) {
@@ -345,7 +334,6 @@ __global__ __launch_bounds__(kTsqrThreads) __attribute__((amdgpu_waves_per_eu(8,
 // MFMA v_mfma_f64_16x16x4: operand A lane l = A(l%16, l/16), B lane l = B(l/16, l%16), result
 // item v of lane l = D(l/16 + 4v, l%16). Y is formed transposed (Y^T = Y0^T - Z^T V^T) so that
 // each 16-lane group of a store writes 16 consecutive rows of one column.
-typedef double wy4 __attribute__((ext_vector_type(4)));
 constexpr int kWyThreads = 512;  // 8 waves
 constexpr int kWyLd = kPMax + 1;
 
@@ -356,8 +344,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
   if (a.st && a.st->done) return;
   const int p = side_cols(a.st, a.ncols, side);
   const int block = apply_block(a.st, a.sel, side, a.block_rows);
-  const int oc = apply_cols(a.st, a.sel, p);  // columns of T_par and of Y
-  if (block < 0 || oc <= 0) return;
+  if (block < 0) return;
   const int64_t row0 = (int64_t)block * a.block_rows;
   const int nr = (int)min((int64_t)a.block_rows, a.rows - row0);
   if (p <= 0 || nr <= 0) return;
@@ -367,14 +354,13 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
   constexpr int kWaves = kWyThreads / 64;
   __shared__ double Vs[kHalf * kWyLd];  // V(r, c) of one half at Vs[r kWyLd + c], zero past p / nr
   __shared__ double S[kPMax * kWyLd];   // v_i . v_k (upper tiles; the rest zero)
-  __shared__ double XZ[kPMax * kWyLd];  // X, then Z in place; zero outside p x oc
+  __shared__ double XZ[kPMax * kWyLd];  // X, then Z in place; zero outside p x p
   __shared__ double tsh[kPMax];
   const double* V = a.V[side] + row0;  // V(r, c) = V[r + c ldv], r < nr, c < p
   const int64_t ldv = a.ldv;
   const double* T = a.T[side];
   const int64_t toff = (int64_t)block * a.pmax;
   const int pt = (p + 15) >> 4;  // 16-column tiles in use
-  const int ot = (oc + 15) >> 4;  // of Y's columns
   const int pk = (p + 3) >> 2;   // 4-row steps over p
   const int ntiles = pt * (pt + 1) / 2;
 
@@ -411,14 +397,14 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
       const int e = t + kWyThreads * m, r = e % kHalf, c = e / kHalf;
       raw[h][m] = V[min(h * kHalf + r, nr - 1) + (int64_t)min(c, p - 1) * ldv];
     }
-  // and the parent piece T_par (p x oc), kept in registers until V's staging buffer is free
+  // and the parent piece T_par (p x p), kept in registers until V's staging buffer is free
   constexpr int kTPer = kPMax * kPMax / kWyThreads;  // 8
   double tpre[kTPer];
   if (T) {
 #pragma unroll
     for (int m = 0; m < kTPer; ++m) {
       const int e = t + kWyThreads * m, r = e % kPMax, c = e / kPMax;
-      tpre[m] = T[toff + min(r, p - 1) + (int64_t)min(c, oc - 1) * a.ldt];
+      tpre[m] = T[toff + min(r, p - 1) + (int64_t)min(c, p - 1) * a.ldt];
     }
   }
 
@@ -450,20 +436,20 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const int q = wave + kWaves * m;
-        if (q >= pt * ot) continue;
-        const int I = q / ot, J = q % ot;
+        if (q >= pt * pt) continue;
+        const int I = q / pt, J = q % pt;
         for (int k0 = 4 * I; k0 < pk; k0 += 4) {
           double tv[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
-            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, oc - 1) * a.ldt];
+            tv[u] = T[toff + min(r, p - 1) + (int64_t)min(16 * J + lr, p - 1) * a.ldt];
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = 4 * (k0 + u) + lk;
             keep_loaded(tv[u]);
-            const double b = (r < p && 16 * J + lr < oc) ? tv[u] : 0.0;
+            const double b = (r < p && 16 * J + lr < p) ? tv[u] : 0.0;
             xacc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Vs[r * kWyLd + 16 * I + lr], b, xacc[m], 0, 0, 0);
           }
         }
@@ -485,13 +471,13 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     __syncthreads();
     }
   }
-  // V's staging buffer now holds T_par (zero outside p x oc) for the final product
+  // V's staging buffer now holds T_par (zero outside p x p) for the final product
   if (T) {
 #pragma unroll
     for (int m = 0; m < kTPer; ++m) {
       const int e = t + kWyThreads * m, r = e % kPMax, c = e / kPMax;
       keep_loaded(tpre[m]);
-      Vs[r * kWyLd + c] = (r < p && c < oc) ? tpre[m] : 0.0;
+      Vs[r * kWyLd + c] = (r < p && c < p) ? tpre[m] : 0.0;
     }
   }
 #pragma unroll
@@ -504,8 +490,8 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const int q = wave + kWaves * m;
-      if (q >= pt * ot) continue;
-      const int I = q / ot, J = q % ot;
+      if (q >= pt * pt) continue;
+      const int I = q / pt, J = q % pt;
 #pragma unroll
       for (int v = 0; v < 4; ++v) XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr] = xacc[m][v];
     }
@@ -539,8 +525,8 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     }
     __syncthreads();
     if (b == 0) break;
-    for (int q = wave; q < b * ot; q += kWaves) {  // tile (I, J): rows 16 I, columns 16 J
-      const int I = q / ot, J = q % ot;
+    for (int q = wave; q < b * pt; q += kWaves) {  // tile (I, J): rows 16 I, columns 16 J
+      const int I = q / pt, J = q % pt;
       wy4 acc;
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[v] = XZ[(16 * I + lk + 4 * v) * kWyLd + 16 * J + lr];
@@ -562,7 +548,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
     const int row = 16 * R + lr;
     if (16 * R >= nr) continue;  // uniform
     wy4 acc[4];
-    if (T) {  // Y0 = [T_par; 0], T_par staged in LDS (zero outside p x oc)
+    if (T) {  // Y0 = [T_par; 0], T_par staged in LDS (zero outside p x p)
 #pragma unroll
       for (int J = 0; J < 4; ++J)
 #pragma unroll
@@ -579,7 +565,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
       const double* Zk = XZ + (4 * ks + lk) * kWyLd + lr;
 #pragma unroll
       for (int J = 0; J < 4; ++J)
-        if (J < ot) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], h == 0 ? vb0[ks] : vb1[ks], acc[J], 0, 0, 0);
+        if (J < pt) acc[J] = __builtin_amdgcn_mfma_f64_16x16x4f64(Zk[16 * J], h == 0 ? vb0[ks] : vb1[ks], acc[J], 0, 0, 0);
     }
     if (row < nr) {
 #pragma unroll
@@ -587,7 +573,7 @@ __global__ __launch_bounds__(kWyThreads) void k_tsqr_apply_wy(Src in) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int col = 16 * J + lk + 4 * v;
-          if (col < oc) Y[row + (int64_t)col * a.ldy] = acc[J][v];
+          if (col < p) Y[row + (int64_t)col * a.ldy] = acc[J][v];
         }
     }
   }
@@ -819,7 +805,9 @@ __global__ __launch_bounds__(kWyThreads) __attribute__((amdgpu_waves_per_eu(4, 4
 // Tree layout: level 0 factors n rows in blocks of kTsqrRows; each level above stacks the R
 // factors of g = kTsqrRows / pmax blocks. `get(bytes)` supplies each buffer (nullptr: failure);
 // buffers of sides >= nsides, and level 0's Y when Q is written to the caller's matrix
-// (level0_y false), are not requested.
+// (level0_y false), are not requested. tau is requested for panel trees, too, which do not use
+// it: the tree's size, and with it the largest n of the allocation-free entry point and a context's
+// bytes, do not depend on the kernels.
 template <typename Get>
 static int tsqr_layout(TsqrPlan* p, int64_t n, int pmax, int nsides, bool level0_y, Get&& get) {
   if (pmax < 1 || pmax > kPMax || n < 1) return LRP_EINVAL;
@@ -906,7 +894,7 @@ static int factor_levels(const TsqrPlan& p, const TsqrIO& io, hipStream_t s) {
   return launch_status();
 }
 
-// Level L's part of Q from its parent's, o.T of nT rows (null: identity), into o.Y.
+// Level L's part of Q from its parent's, o.T (null: identity), into o.Y.
 static int apply_level(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOut& o, hipStream_t s) {
   if (!io.columns) return tsqr_panel_apply(p, L, io, o, s);
   const TsqrLevel& lv = p.lev[L];
@@ -928,7 +916,8 @@ static int apply_level(const TsqrPlan& p, int L, const TsqrIO& io, const ApplyOu
     a.Y[q] = o.Y[q];
   }
   const int nblocks = o.sel.pick ? p.pmax : lv.nblocks;
-  if ((int64_t)nblocks * io.nsides > kCUs)
+  // the fold's columns (out_nb) are the lean build's alone: it starts where the leaves have 512 blocks
+  if (o.sel.out_nb >= 0 || (int64_t)nblocks * io.nsides > kCUs)
     LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_lean<ApplyArgs>, k_tsqr_apply_lean<GroupRef>, dim3(nblocks, io.nsides), dim3(kWyThreads), 0, s, a);
   else
     LRP_LAUNCH_G(K_TSQR_APPLY, k_tsqr_apply_wy<ApplyArgs>, k_tsqr_apply_wy<GroupRef>, dim3(nblocks, io.nsides), dim3(kWyThreads), 0, s, a);

@@ -46,17 +46,6 @@ struct PanelApplyArgs {
   uint8_t cls[4];
 };
 
-// An empty asm statement that takes a loaded value as input and output: the load must then
-// complete unconditionally before it, so a following select on a lane condition cannot be
-// turned into a branch around the load (which would serialise the loads, each with its own wait).
-__device__ inline void keep_loaded(double& v) { asm volatile("" : "+v"(v)); }
-__device__ inline void keep_loaded(float& v) { asm volatile("" : "+v"(v)); }
-
-__device__ inline int side_cols(const DevState* st, const int* fixed, int side) {
-  return st ? st->ncols[side] : fixed[side];
-}
-
-typedef double wy4 __attribute__((ext_vector_type(4)));
 constexpr int kWyThreads = 256;           // 4 waves, 16 columns each
 constexpr int kPanel = 16;                // columns per panel
 constexpr int kVLd = kPanel + 1;          // LDS row stride of a panel (odd: the transposed reads spread over the banks)
@@ -657,7 +646,6 @@ static void tile_classes(const TsqrPlan& p, int L, uint8_t (&cls)[4]) {
     cls[P] |= (uint8_t)(1 << P);  // the diagonal tile
   }
 }
-
 
 int tsqr_panel_factor(const TsqrPlan& p, int L, const TsqrIO& io, hipStream_t s) {
   const TsqrLevel& lv = p.lev[L];
