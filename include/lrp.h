@@ -248,7 +248,9 @@ int lrp_set_index_sets(lrp_ctx* ctx, int32_t npasses, const int64_t* I, const in
 
 /* One kernel class of a profiled solve (host struct filled by lrp_get_profile). */
 typedef struct lrp_kernel_time {
-  const char* name;  /* kernel name (static string owned by the library) */
+  const char* name;  /* class name (static string owned by the library): that of its kernels, or
+                        what theirs begin with. k_tsqr_factor and k_tsqr_apply hold the thin
+                        QRs' kernels of either kind, by columns (FP64) and by panels (mixed) */
   int32_t launches;  /* launches in the last solve */
   double ms;         /* their summed device time, milliseconds, each launch timed by start and
                         stop events attached to its dispatch (hipExtLaunchKernelGGL; a copy by

@@ -227,8 +227,8 @@ int tsqr_run(const TsqrPlan& p, const TsqrIO& io, hipStream_t s);
 // of Q that the core and the indicator read, bit for bit as tsqr_run forms them. tsqr_fold: pa's product
 // (pa.Q is not read), through level 1's V, which is free by then. What it saves, three quarters of the
 // product and of its traffic, has to pay for the launch of the picked blocks: ms per solve without and
-// with it at n = 65535 1.56, 1.55 (mixed, cap 64); 131071 2.19, 2.14; 262143 3.15, 3.00; 2^20 - 1 9.44,
-// 8.39, and in FP64 at caps 32 and 64 11.4, 10.1 and 21.9, 20.2.
+// with it for 30 bumps of widths 0.05 to 0.2 at n = 65535 1.56, 1.55 (mixed, cap 64); 131071 2.19, 2.14;
+// 262143 3.15, 3.00; 2^20 - 1 9.44, 8.39 (rank 16), and 21.9, 20.2 in FP64 (rank 26).
 constexpr int64_t kTsqrFoldRows = int64_t(1) << 16;
 bool tsqr_can_fold(const TsqrPlan& p);
 int tsqr_run_rows(const TsqrPlan& p, const TsqrIO& io, bool rows, hipStream_t s);
